@@ -18,10 +18,17 @@
 // branch) is divided out and sweeps over the three SU(2) subgroups (Cabibbo-Marinari), each taking the
 // subgroup element that maximises the objective, run until a sweep moves no element by more than 1e-15.
 //
-// One thread per (site, field); blockIdx.y selects the field, so a wavefront covers 64 consecutive sites
-// of one field. Every level is FP64. Input and output links use the natural layout [4][V][3][3] complex128
-// (a link is 9 consecutive double2); the intermediate fields live in the caller's workspace as planes
-// [9][V] double2 per field. All directions are periodic.
+// One thread per (site, field). Every level is FP64. Input and output links use the natural layout [4][V][3][3]
+// complex128 (a link is 9 consecutive double2); a first launch copies the input into planes, and the intermediate
+// fields are planes in the caller's workspace. All directions are periodic.
+//
+// What bounds it. A staple pair reads six links, nearly all past the 32 KB L1: measured at 20^3x64, levels 1 to 3
+// drew 10.4 to 11.3 TB/s from the L2, whatever the order of the blocks, with the FP64 units 40 to 60% busy. So the
+// levels read planes (natural links of 144 bytes a lane apart cost four times the address cycles), store and read two
+// rows of the projected links, and a projection takes about 500 multiply-adds where a 60-term series took 1,700:
+// 3.13 -> 1.53 ms a smearing (planes 0.11, levels 0.52 + 0.59 + 0.31 ms; before 0.97 + 1.48 + 0.71 ms). Measured and
+// left: one thread per run of sites along the staple direction, three loads a staple pair (2.2 ms: the runs along x
+// lose their coalescing, and the carried links spill), one thread for lv1(mu, eta) and lv1(eta, mu) (1.68 ms, spills).
 #include "sp_launch.h"
 
 namespace sp {
@@ -30,40 +37,38 @@ namespace {
 using C = Cx<double>;
 using M3 = Su3<double>;
 
+// Exact n / d for 0 <= n < 2^25 by one multiplication: M = ceil(2^(25 + l) / d) with 2^l >= d, so that the excess
+// n (M d - 2^(25 + l)) / 2^(25 + l) stays below one.
+struct Div {
+    unsigned M;
+    int shift;
+    __device__ __forceinline__ int operator()(int n) const { return (int)(((unsigned long long)(unsigned)n * M) >> shift); }
+};
+Div div_by(int d) {
+    int l = 0;
+    while ((1L << l) < d) ++l;
+    return {(unsigned)(((1ull << (25 + l)) + d - 1) / d), 25 + l};
+}
+
 struct HypGeom {
     int L[4];       // extents X, Y, Z, T
     int stride[4];  // 1, X, XY, XYZ
+    Div by_L[4], by_stride[4];
     int V;
 };
 
-__device__ __forceinline__ int hop(const HypGeom& g, int s, int mu, int d) {
-    const int c = (s / g.stride[mu]) % g.L[mu];
-    const int c1 = c + d;
-    int s1 = s + d * g.stride[mu];
-    if (c1 == g.L[mu]) s1 -= g.L[mu] * g.stride[mu];
-    if (c1 < 0) s1 += g.L[mu] * g.stride[mu];
-    return s1;
-}
-
-// A link field: element (site s, entry j) at p[s * ss + j * ps] (double2 units).
-struct LinkField {
-    const double2* p;
-    long ss, ps;
+// Byte offsets (16 per site) of the neighbours of a site in a uniform direction mu, periodic. Hops in different
+// directions commute, so the offset of n - eta + mu is that of -eta plus that of +mu.
+struct Hop {
+    unsigned f, b;
 };
-
-__device__ __forceinline__ M3 ld(const LinkField& f, int s) {
-    M3 m;
-#pragma unroll
-    for (int j = 0; j < 9; ++j) {
-        const double2 v = f.p[(long)s * f.ss + (long)j * f.ps];
-        m.e[j / 3][j % 3] = {v.x, v.y};
-    }
-    return m;
+__device__ __forceinline__ Hop hop_at(const HypGeom& g, int c, int mu) {
+    const int st = 16 * g.stride[mu], wrap = (g.L[mu] - 1) * st;
+    return {(unsigned)(c == g.L[mu] - 1 ? -wrap : st), (unsigned)(c == 0 ? wrap : -st)};
 }
-
-__device__ __forceinline__ void st(double2* p, long ss, long ps, int s, const M3& m) {
-#pragma unroll
-    for (int j = 0; j < 9; ++j) p[(long)s * ss + (long)j * ps] = make_double2(m.e[j / 3][j % 3].re, m.e[j / 3][j % 3].im);
+__device__ __forceinline__ Hop hop(const HypGeom& g, int s, int mu) {
+    const int q = g.by_stride[mu](s);
+    return hop_at(g, q - g.by_L[mu](q) * g.L[mu], mu);
 }
 
 __device__ __forceinline__ C cmul(C a, C b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
@@ -72,78 +77,124 @@ __device__ __forceinline__ C cmulc(C a, C b) { return {a.re * b.re + a.im * b.im
 __device__ __forceinline__ C cadd(C a, C b) { return {a.re + b.re, a.im + b.im}; }
 __device__ __forceinline__ C csub(C a, C b) { return {a.re - b.re, a.im - b.im}; }
 
-// a b
-__device__ __forceinline__ M3 mul(const M3& a, const M3& b) {
-    M3 r;
+// acc + a b, acc + a conj(b), acc + conj(a) b as four fused multiply-adds
+__device__ __forceinline__ C fmacc(C acc, C a, C b) {
+    return {fma(-a.im, b.im, fma(a.re, b.re, acc.re)), fma(a.im, b.re, fma(a.re, b.im, acc.im))};
+}
+__device__ __forceinline__ C fmaccc(C acc, C a, C b) {
+    return {fma(a.im, b.im, fma(a.re, b.re, acc.re)), fma(a.im, b.re, fma(-a.re, b.im, acc.im))};
+}
+
+// Row 2 of an SU(3) matrix from the other two: the conjugate of their cross product.
+__device__ __forceinline__ void row2(M3& m) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const C a = m.e[0][(j + 1) % 3], b = m.e[1][(j + 2) % 3], c = m.e[0][(j + 2) % 3], d = m.e[1][(j + 1) % 3];
+        m.e[2][j].re = fma(c.im, d.im, fma(-c.re, d.re, fma(-a.im, b.im, a.re * b.re)));
+        m.e[2][j].im = fma(c.im, d.re, fma(c.re, d.im, fma(-a.im, b.re, -a.re * b.im)));
+    }
+}
+
+// Intermediate links are stored as planes of double2, one per matrix entry, V sites each: rows 0 and 1 of the projected
+// levels (ROWS = 2; row 2 of an SU(3) matrix is the conjugate cross product of the other two, formed again after a
+// load: 24 multiply-adds against a third of the bytes, on a path bound by them), all three of the input links (ROWS = 3).
+// A link sits at byte offset off = 16 s of its planes: a uniform plane address plus one 32-bit offset per lane (a plane
+// holds less than 2^29 bytes), so that the loads of a link share their address registers.
+template <int ROWS>
+__device__ __forceinline__ M3 ld(const char* p, size_t plane, unsigned off) {
+    M3 m;
+#pragma unroll
+    for (int j = 0; j < 3 * ROWS; ++j) {
+        const double2 v = *(const double2*)(p + j * plane + off);
+        m.e[j / 3][j % 3] = {v.x, v.y};
+    }
+    if constexpr (ROWS == 2) row2(m);
+    return m;
+}
+
+template <int ROWS>
+__device__ __forceinline__ void st(char* p, size_t plane, unsigned off, const M3& m) {
+#pragma unroll
+    for (int j = 0; j < 3 * ROWS; ++j)
+        *(double2*)(p + j * plane + off) = make_double2(m.e[j / 3][j % 3].re, m.e[j / 3][j % 3].im);
+}
+
+__device__ __forceinline__ void scale(M3& w, double c) {
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            C s = cmul(a.e[i][0], b.e[0][j]);
-            s = cadd(s, cmul(a.e[i][1], b.e[1][j]));
-            r.e[i][j] = cadd(s, cmul(a.e[i][2], b.e[2][j]));
+            w.e[i][j].re *= c;
+            w.e[i][j].im *= c;
         }
+}
+
+// Rows 0 .. ROWS-1 of a b, a b^dag and a^dag b.
+template <int ROWS>
+__device__ __forceinline__ M3 mul_rows(const M3& a, const M3& b) {
+    M3 r;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            r.e[i][j] = fmacc(fmacc(cmul(a.e[i][0], b.e[0][j]), a.e[i][1], b.e[1][j]), a.e[i][2], b.e[2][j]);
+    return r;
+}
+template <int ROWS>
+__device__ __forceinline__ M3 mul_nd_rows(const M3& a, const M3& b) {
+    M3 r;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            r.e[i][j] = fmaccc(fmaccc(cmulc(a.e[i][0], b.e[j][0]), a.e[i][1], b.e[j][1]), a.e[i][2], b.e[j][2]);
+    return r;
+}
+template <int ROWS>
+__device__ __forceinline__ M3 mul_dn_rows(const M3& a, const M3& b) {
+    M3 r;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            r.e[i][j] = fmaccc(fmaccc(cmulc(b.e[0][j], a.e[0][i]), b.e[1][j], a.e[1][i]), b.e[2][j], a.e[2][i]);
     return r;
 }
 
-// a b^dag
-__device__ __forceinline__ M3 mul_nd(const M3& a, const M3& b) {
-    M3 r;
+// w += c * [S(x) T(x+eta) S(x+mu)^dag + S(x-eta)^dag T(x-eta) S(x-eta+mu)], S and T in planes. With ROWS = 2 the links
+// are in SU(3), and so are the products: their third row is formed from the other two as well.
+template <int ROWS>
+__device__ __forceinline__ void add_staples(M3& w, double c, size_t plane, const char* S, const char* T, unsigned o,
+                                            unsigned fm, Hop he) {
+    const unsigned pe = o + he.f, me = o + he.b;
+    auto add = [&](M3& p) {
+        if constexpr (ROWS == 2) row2(p);
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+        for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            C s = cmulc(a.e[i][0], b.e[j][0]);
-            s = cadd(s, cmulc(a.e[i][1], b.e[j][1]));
-            r.e[i][j] = cadd(s, cmulc(a.e[i][2], b.e[j][2]));
-        }
-    return r;
-}
-
-// a^dag b
-__device__ __forceinline__ M3 mul_dn(const M3& a, const M3& b) {
-    M3 r;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            C s = cmulc(b.e[0][j], a.e[0][i]);
-            s = cadd(s, cmulc(b.e[1][j], a.e[1][i]));
-            r.e[i][j] = cadd(s, cmulc(b.e[2][j], a.e[2][i]));
-        }
-    return r;
-}
-
-__device__ __forceinline__ void axpy(M3& w, double c, const M3& a) {
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            w.e[i][j].re += c * a.e[i][j].re;
-            w.e[i][j].im += c * a.e[i][j].im;
-        }
-}
-
-// w += c * [S(x) T(x+eta) S(x+mu)^dag + S(x-eta)^dag T(x-eta) S(x-eta+mu)]
-__device__ __forceinline__ void add_staples(M3& w, double c, const HypGeom& g, const LinkField& S, const LinkField& T,
-                                            int s, int mu, int eta) {
-    const int s_pe = hop(g, s, eta, +1), s_pm = hop(g, s, mu, +1), s_me = hop(g, s, eta, -1);
-    const int s_me_pm = hop(g, s_me, mu, +1);
-    axpy(w, c, mul_nd(mul(ld(S, s), ld(T, s_pe)), ld(S, s_pm)));
-    axpy(w, c, mul(mul_dn(ld(S, s_me), ld(T, s_me)), ld(S, s_me_pm)));
+            for (int j = 0; j < 3; ++j)
+                w.e[i][j] = {fma(c, p.e[i][j].re, w.e[i][j].re), fma(c, p.e[i][j].im, w.e[i][j].im)};
+    };
+    M3 a = mul_rows<ROWS>(ld<ROWS>(S, plane, o), ld<ROWS>(T, plane, pe));
+    a = mul_nd_rows<ROWS>(a, ld<ROWS>(S, plane, o + fm));
+    add(a);
+    a = mul_dn_rows<ROWS>(ld<ROWS>(S, plane, me), ld<ROWS>(T, plane, me));
+    a = mul_rows<ROWS>(a, ld<ROWS>(S, plane, me + fm));
+    add(a);
 }
 
 // rows of the cofactor matrix are cross products of the other two rows
 __device__ __forceinline__ void cross(const C* a, const C* b, C* out) {
-    out[0] = csub(cmul(a[1], b[2]), cmul(a[2], b[1]));
-    out[1] = csub(cmul(a[2], b[0]), cmul(a[0], b[2]));
-    out[2] = csub(cmul(a[0], b[1]), cmul(a[1], b[0]));
+    auto minor = [](C p, C q, C r, C t) { return fmacc(cmul(p, q), {-r.re, -r.im}, t); };  // p q - r t
+    out[0] = minor(a[1], b[2], a[2], b[1]);
+    out[1] = minor(a[2], b[0], a[0], b[2]);
+    out[2] = minor(a[0], b[1], a[1], b[0]);
 }
 
 __device__ __forceinline__ C det3(const M3& x) {
     C c[3];
     cross(x.e[1], x.e[2], c);
-    return cadd(cadd(cmul(x.e[0][0], c[0]), cmul(x.e[0][1], c[1])), cmul(x.e[0][2], c[2]));
+    return fmacc(fmacc(cmul(x.e[0][0], c[0]), x.e[0][1], c[1]), x.e[0][2], c[2]);
 }
 
 // The unitary polar factor of w by Newton's iteration with determinant scaling. X^-dag = conj(cof(X)) /
@@ -232,7 +283,7 @@ __device__ __forceinline__ bool proj_series(const M3& w, const M3& up, M3& x) {
     constexpr double c[7] = {1.0, 1.0 / 6, 3.0 / 40, 5.0 / 112, 35.0 / 1152, 63.0 / 2816, 231.0 / 13312};
     const C du = det3(up);
     const double phi = atan2(du.im, du.re);
-    M3 h = mul_dn(up, w);
+    M3 h = mul_dn_rows<3>(up, w);
     hermitize(h);
     M3 cof;
     cross(h.e[1], h.e[2], cof.e[0]);
@@ -319,7 +370,7 @@ __device__ __forceinline__ bool proj_series(const M3& w, const M3& up, M3& x) {
         for (int a = 0; a < 3; ++a) ev[a] = {cc[a].re * rq, cc[a].im * rq};
         ev[0].re += 1.0;
     }
-    const M3 g2 = mul(g, g);
+    const M3 g2 = mul_rows<3>(g, g);
     M3 e;
 #pragma unroll
     for (int i = 0; i < 3; ++i)
@@ -329,147 +380,182 @@ __device__ __forceinline__ bool proj_series(const M3& w, const M3& up, M3& x) {
             if (i == j) s = cadd(s, ev[0]);
             e.e[i][j] = s;
         }
-    x = mul(up, e);
+    x = mul_rows<3>(up, e);
     return true;
 }
 
-// Polynomials a0 + a1 E + a2 E^2 in a traceless Hermitian 3x3 matrix E, reduced by its characteristic
-// polynomial E^3 = -e2 E + e3 (e2 = -tr(E^2)/2, e3 = det E).
-template <class T>
-__device__ __forceinline__ void poly_mul(const T (&a)[3], const T (&b)[3], double e2, double e3, T (&r)[3]) {
-    T c[5];
-#pragma unroll
-    for (int q = 0; q < 5; ++q) c[q] = T(0.0);
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) c[i + j] = c[i + j] + a[i] * b[j];
-#pragma unroll
-    for (int q = 4; q >= 3; --q) {  // E^q = -e2 E^(q-2) + e3 E^(q-3)
-        c[q - 2] = c[q - 2] - c[q] * e2;
-        c[q - 3] = c[q - 3] + c[q] * e3;
-    }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) r[q] = c[q];
+// 1 / x and 1 / sqrt(x) from the hardware estimates by two Newton steps each (within an ulp or two for normal x; zero,
+// infinite, subnormal and NaN arguments give values that the caller's tests refuse).
+__device__ __forceinline__ double rcp(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ __forceinline__ double rsq(double x) {
+    double r = __builtin_amdgcn_rsq(x);
+    r = fma(fma(-x * r, r, 1.0), 0.5 * r, r);
+    return fma(fma(-x * r, r, 1.0), 0.5 * r, r);
 }
 
-// complex scalar with the operators poly_mul needs
-struct Z {
-    double re, im;
-    __device__ Z() = default;
-    __device__ constexpr Z(double r) : re(r), im(0.0) {}
-    __device__ constexpr Z(double r, double i) : re(r), im(i) {}
-};
-__device__ __forceinline__ Z operator+(Z a, Z b) { return {a.re + b.re, a.im + b.im}; }
-__device__ __forceinline__ Z operator-(Z a, Z b) { return {a.re - b.re, a.im - b.im}; }
-__device__ __forceinline__ Z operator*(Z a, Z b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
-__device__ __forceinline__ Z operator*(Z a, double s) { return {a.re * s, a.im * s}; }
+// r = a b for polynomials a0 + a1 E + a2 E^2 in a traceless 3x3 matrix E, reduced by its characteristic polynomial
+// E^3 = -e2 E + e3 (e2 = -tr(E^2)/2, e3 = det E).
+__device__ __forceinline__ void poly_mul(const double (&a)[3], const double (&b)[3], double e2, double e3, double (&r)[3]) {
+    const double c4 = a[2] * b[2], c3 = a[1] * b[2] + a[2] * b[1];
+    r[2] = a[0] * b[2] + a[1] * b[1] + a[2] * b[0] - c4 * e2;
+    r[1] = a[0] * b[1] + a[1] * b[0] - c3 * e2 + c4 * e3;
+    r[0] = a[0] * b[0] + c3 * e3;
+}
 
 // The same maximiser as proj_series, written entirely as a function of S = W^dag W: the polar factor is
-// W S^-1/2 and H^-1 = S^-1/2, so X = W F(S) with F = S^-1/2 exp(i asin(mu S^-1/2)), det W = |det W| e^{i phi}.
-// With s0 = tr S / 3 and E = S / s0 - I (traceless), S^-1/2 = s0^-1/2 sum_k binom(-1/2, k) E^k; all series
-// are carried as coefficients of I, E, E^2, so the matrix products are S, E^2 and W F. Used when
-// |E|_F <= 1/2 (60 terms of the binomial series then leave less than 1e-17) and |mu| |S^-1/2|_F <= 0.06;
-// returns false otherwise.
+// W S^-1/2 and H^-1 = S^-1/2, so X = W F with F = S^-1/2 exp(i Theta), sin Theta = Y = mu S^-1/2 and det W =
+// |det W| e^{i phi}. With s0 = tr S / 3 and E = S / s0 - 1 (traceless) every function of S is three scalar
+// coefficients of 1, E and E^2:
+//   P = (1 + E)^1/2 has the symmetric functions u, v, w of its eigenvalues with w^2 = det(1 + E), u^2 = 3 + 2 v and
+//   v^2 = 3 + e2 + 2 u w; u is the root next to its series start, by Newton's steps with a fixed slope (the
+//   derivative 2 (u v - w) is the product of the eigenvalues' pairwise sums, so the root is well conditioned);
+//   G = (1 + E)^-1/2 follows from the characteristic polynomial P^3 = u P^2 - v P + w (Hasenfratz, Hoffmann and
+//   Schaefer, JHEP 0705 (2007) 029, give the coefficients), and G^2 = (1 + E)^-1 from that of 1 + E;
+//   exp(i Theta) = (1 - Y^2)^1/2 + i Y, so only the even part needs a series.
+// mu solves tr asin(mu G) = -phi, by fixed-point steps from -phi / tr G that gain a factor of about 2 / Y^2 each.
+// The series run to Y^5 (Y at most 1e-3 in norm: omitted terms below 1e-19), or to Y^13 in the lanes that need it.
+// Used when |E|_F <= 1/2 and |Y|_F <= 0.06 (omitted terms below 1e-17, and the principal phases are the maximum);
+// returns false otherwise (x is then meaningless): the tests gather in one flag, so that nothing but the long series
+// sits under a branch.
 __device__ __forceinline__ bool proj_direct(const M3& w, M3& x) {
-    constexpr double c[7] = {1.0, 1.0 / 6, 3.0 / 40, 5.0 / 112, 35.0 / 1152, 63.0 / 2816, 231.0 / 13312};
-    M3 s = mul_dn(w, w);
-    hermitize(s);
-    const double s0 = (s.e[0][0].re + s.e[1][1].re + s.e[2][2].re) * (1.0 / 3.0);
-    if (!(s0 > 0.0) || !isfinite(s0)) return false;
-    const double rs0 = 1.0 / s0;
-    M3 e;
-    double t2 = 0.0;  // tr E^2 = |E|_F^2
+    // S = W^dag W: real diagonal, upper triangle
+    double dg[3];
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < 3; ++i) {
+        dg[i] = 0.0;
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            e.e[i][j] = {s.e[i][j].re * rs0 - (i == j ? 1.0 : 0.0), s.e[i][j].im * rs0};
-            t2 += e.e[i][j].re * e.e[i][j].re + e.e[i][j].im * e.e[i][j].im;
-        }
-    if (!(t2 <= 0.25)) return false;
-    const double e2 = -0.5 * t2, e3 = det3(e).re;
-    // G = S^-1/2
-    double g[3] = {0.0, 0.0, 0.0}, pk[3] = {1.0, 0.0, 0.0}, bk = 1.0;
-#pragma unroll
-    for (int kk = 0; kk < 60; ++kk) {
-#pragma unroll
-        for (int q = 0; q < 3; ++q) g[q] += bk * pk[q];
-        const double a0 = pk[0], a1 = pk[1], a2 = pk[2];  // times E
-        pk[0] = a2 * e3;
-        pk[1] = a0 - a2 * e2;
-        pk[2] = a1;
-        bk *= -(2.0 * kk + 1.0) / (2.0 * kk + 2.0);
+        for (int k = 0; k < 3; ++k) dg[i] += w.e[k][i].re * w.e[k][i].re + w.e[k][i].im * w.e[k][i].im;
     }
-    const double rsq = 1.0 / sqrt(s0);
+    auto sij = [&](int i, int j) {
+        return fmaccc(fmaccc(cmulc(w.e[0][j], w.e[0][i]), w.e[1][j], w.e[1][i]), w.e[2][j], w.e[2][i]);
+    };
+    C o01 = sij(0, 1), o02 = sij(0, 2), o12 = sij(1, 2);
+    const double s0 = (dg[0] + dg[1] + dg[2]) * (1.0 / 3.0);
+    bool ok = s0 > 0.0 && isfinite(s0);
+    const double rsq0 = rsq(s0), rs0 = rsq0 * rsq0;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) g[q] *= rsq;
-    const C dw = det3(w);
-    const double phi = atan2(dw.im, dw.re);
-    double g2[3];
-    poly_mul(g, g, e2, e3, g2);
+    for (int i = 0; i < 3; ++i) dg[i] = dg[i] * rs0 - 1.0;
+    o01 = {o01.re * rs0, o01.im * rs0};
+    o02 = {o02.re * rs0, o02.im * rs0};
+    o12 = {o12.re * rs0, o12.im * rs0};
+    const double n01 = o01.re * o01.re + o01.im * o01.im, n02 = o02.re * o02.re + o02.im * o02.im,
+                 n12 = o12.re * o12.re + o12.im * o12.im;
+    const double t2 = dg[0] * dg[0] + dg[1] * dg[1] + dg[2] * dg[2] + 2.0 * (n01 + n02 + n12);  // tr E^2
+    ok &= t2 <= 0.25;
+    const C o = cmul(o01, o12);
+    const double e2 = -0.5 * t2, e3 = dg[0] * dg[1] * dg[2] + 2.0 * (o.re * o02.re + o.im * o02.im) - dg[0] * n12 -
+                                      dg[1] * n02 - dg[2] * n01;
+    const double c3 = 1.0 + e2 + e3, rww = rsq(c3), ww = c3 * rww, rc3 = rww * rww;
+    double u = 3.0 - t2 * (0.125 + t2 * (5.0 / 256.0)) + e3 * (3.0 / 16.0);
+    const double slope = __builtin_amdgcn_rcp(u * (u * u - 3.0) - 2.0 * ww);
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        const double hv = 0.5 * (u * u - 3.0);
+        u -= (hv * hv - (3.0 + e2) - 2.0 * u * ww) * slope;
+    }
+    const double v = 0.5 * (u * u - 3.0), uv = u * v;
+    const double rden = rww * rcp(uv - ww);
+    const double f0 = (uv * v - ww * (u * u + v)) * rden, f1 = (2.0 * uv - ww - u * u * u) * rden, f2 = u * rden;
+    const double h[3] = {(1.0 + e2) * rc3, -rc3, rc3};  // (1 + E)^-1
+    double g0[3] = {f0 + f1 + f2, f1 + 2.0 * f2, f2}, g1[3], g2[3];
+    poly_mul(g0, h, e2, e3, g1);
+    poly_mul(g1, h, e2, e3, g2);
+    const C d = det3(w);
+    const double q = d.im * rcp(d.re);
+    // |phi| <= sqrt(3) |Y|_F or so: phases past 0.11 are refused below anyway
+    ok &= d.re > 0.0 && fabs(q) <= 0.12;
+    const double q2 = q * q;
+    double at = -1.0 / 15.0;
+#pragma unroll
+    for (int k = 13; k >= 1; k -= 2) at = at * q2 + (k % 4 == 1 ? 1.0 : -1.0) / k;
+    const double phi = at * q;
     auto trace = [&](const double (&a)[3]) { return 3.0 * a[0] + a[2] * t2; };
-    // odd powers of G and their traces
-    double gp[7][3], p[7];
+    const double rp = rcp(trace(g0)), mu0 = -phi * rp;
+    const double b1 = trace(g1) * rp * (1.0 / 6.0), b2 = trace(g2) * rp * (3.0 / 40.0);
+    double mu = mu0;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) gp[0][q] = g[q];
+    for (int it = 0; it < 3; ++it) {
+        const double z = mu * mu;
+        mu = mu0 - mu * z * (b1 + b2 * z);
+    }
+    const double hn2 = trace(h);  // |G|_F^2
+    double z = mu * mu;
+    double a[3];
 #pragma unroll
-    for (int n = 1; n < 7; ++n) poly_mul(gp[n - 1], g2, e2, e3, gp[n]);
+    for (int k = 0; k < 3; ++k) a[k] = g0[k] - z * (0.5 * g1[k] + 0.125 * z * g2[k]);
+    if (ok && !(z * hn2 <= 1e-6)) {
+        // terms n = 3..6: G^(2n+1) from the one before
+        constexpr double ca[4] = {5.0 / 112, 35.0 / 1152, 63.0 / 2816, 231.0 / 13312};
+        constexpr double cs[4] = {1.0 / 16, 5.0 / 128, 7.0 / 256, 21.0 / 1024};
+        double gn[4][3], bn[4];
+        poly_mul(g2, h, e2, e3, gn[0]);
 #pragma unroll
-    for (int n = 0; n < 7; ++n) p[n] = trace(gp[n]);
-    double mu = -phi / p[0];
+        for (int n = 1; n < 4; ++n) poly_mul(gn[n - 1], h, e2, e3, gn[n]);
 #pragma unroll
-    for (int it = 0; it < 6; ++it) {
-        const double m2 = mu * mu;
-        double f = 0.0, df = 0.0, mp = 1.0;
-#pragma unroll
-        for (int n = 0; n < 7; ++n) {
-            df += c[n] * (2 * n + 1) * p[n] * mp;
-            f += c[n] * p[n] * mp * mu;
-            mp *= m2;
+        for (int n = 0; n < 4; ++n) bn[n] = ca[n] * trace(gn[n]) * rp;
+        for (int it = 0; it < 6; ++it) {
+            z = mu * mu;
+            mu = mu0 - mu * z * (b1 + z * (b2 + z * (bn[0] + z * (bn[1] + z * (bn[2] + z * bn[3])))));
         }
-        mu -= (f + phi) / df;
-    }
-    if (!(fabs(mu) * sqrt(trace(g2)) <= 0.06)) return false;
-    double th[3] = {0.0, 0.0, 0.0}, mp = mu;
+        z = mu * mu;
+        ok = z * hn2 <= 0.06 * 0.06;
 #pragma unroll
-    for (int n = 0; n < 7; ++n) {
-#pragma unroll
-        for (int q = 0; q < 3; ++q) th[q] += c[n] * mp * gp[n][q];
-        mp *= mu * mu;
+        for (int k = 0; k < 3; ++k)
+            a[k] = g0[k] - z * (0.5 * g1[k] + z * (0.125 * g2[k] + z * (cs[0] * gn[0][k] + z * (cs[1] * gn[1][k] +
+                   z * (cs[2] * gn[2][k] + z * cs[3] * gn[3][k])))));
     }
-    const Z ith[3] = {Z(0.0, th[0]), Z(0.0, th[1]), Z(0.0, th[2])};
-    Z ev[3] = {Z(1.0), Z(0.0), Z(0.0)};
+    // F = (a + i mu h) / sqrt(s0): the Hermitian parts P of a and Q of mu h, F = P + i Q
+    double b[3];
 #pragma unroll
-    for (int q = 8; q >= 1; --q) {
-        Z t[3];
-        poly_mul(ith, ev, e2, e3, t);
-        const double rq = 1.0 / q;
-        ev[0] = t[0] * rq + Z(1.0);
-        ev[1] = t[1] * rq;
-        ev[2] = t[2] * rq;
+    for (int k = 0; k < 3; ++k) {
+        a[k] *= rsq0;
+        b[k] = mu * rsq0 * h[k];
     }
-    const Z gz[3] = {Z(g[0]), Z(g[1]), Z(g[2])};
-    Z f[3];
-    poly_mul(gz, ev, e2, e3, f);
-    const M3 ee = mul(e, e);
+    // E^2
+    const double q00 = dg[0] * dg[0] + n01 + n02, q11 = dg[1] * dg[1] + n01 + n12, q22 = dg[2] * dg[2] + n02 + n12;
+    const C e01 = cmulc(o02, o12), e02 = o, e12 = cmulc(o02, o01);  // o02 o12*, o01 o12, o01* o02
+    const C x01 = {(dg[0] + dg[1]) * o01.re + e01.re, (dg[0] + dg[1]) * o01.im + e01.im};
+    const C x02 = {(dg[0] + dg[2]) * o02.re + e02.re, (dg[0] + dg[2]) * o02.im + e02.im};
+    const C x12 = {(dg[1] + dg[2]) * o12.re + e12.re, (dg[1] + dg[2]) * o12.im + e12.im};
     M3 m;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const C a = cmul({f[1].re, f[1].im}, e.e[i][j]), b = cmul({f[2].re, f[2].im}, ee.e[i][j]);
-            m.e[i][j] = {a.re + b.re + (i == j ? f[0].re : 0.0), a.im + b.im + (i == j ? f[0].im : 0.0)};
-        }
-    x = mul(w, m);
-    return true;
+    m.e[0][0] = {a[0] + a[1] * dg[0] + a[2] * q00, b[0] + b[1] * dg[0] + b[2] * q00};
+    m.e[1][1] = {a[0] + a[1] * dg[1] + a[2] * q11, b[0] + b[1] * dg[1] + b[2] * q11};
+    m.e[2][2] = {a[0] + a[1] * dg[2] + a[2] * q22, b[0] + b[1] * dg[2] + b[2] * q22};
+    auto off = [&](C e, C ee, C& up, C& lo) {
+        const C P = {a[1] * e.re + a[2] * ee.re, a[1] * e.im + a[2] * ee.im};
+        const C Q = {b[1] * e.re + b[2] * ee.re, b[1] * e.im + b[2] * ee.im};
+        up = {P.re - Q.im, P.im + Q.re};
+        lo = {P.re + Q.im, Q.re - P.im};
+    };
+    off(o01, x01, m.e[0][1], m.e[1][0]);
+    off(o02, x02, m.e[0][2], m.e[2][0]);
+    off(o12, x12, m.e[1][2], m.e[2][1]);
+    x = mul_rows<3>(w, m);
+    return ok;
 }
 
-__device__ __forceinline__ M3 proj_su3(const M3& w) {
-    M3 y;
-    if (proj_direct(w, y)) return y;
+// The maximiser where proj_direct declines, out of line and through memory (m: W on entry, the maximiser on return),
+// so that the level kernels hold the registers of the usual path only. WAVES per SIMD of the kernels that call it: a
+// called function is allocated for the kernel with the most registers, so kernels of different budgets take their own.
+template <int WAVES>
+__device__ __noinline__ void proj_iterate(double2* m) {
+    M3 w;
+#pragma unroll
+    for (int j = 0; j < 9; ++j) w.e[j / 3][j % 3] = {m[j].x, m[j].y};
+    auto put = [&](const M3& r) {
+#pragma unroll
+        for (int j = 0; j < 9; ++j) m[j] = make_double2(r.e[j / 3][j % 3].re, r.e[j / 3][j % 3].im);
+    };
     M3 x = polar_factor(w);
-    if (proj_series(w, x, y)) return y;
+    M3 y;
+    if (proj_series(w, x, y)) {
+        put(y);
+        return;
+    }
     const C d = det3(x);
     const double th = -atan2(d.im, d.re) / 3.0;
     const C ph = {cos(th), sin(th)};
@@ -492,6 +578,20 @@ __device__ __forceinline__ M3 proj_su3(const M3& w) {
             }
         if (diff2 <= 1e-30) break;
     }
+    put(x);
+}
+
+template <int WAVES>
+__device__ __forceinline__ M3 proj_su3(const M3& w) {
+    M3 x;
+    if (!proj_direct(w, x)) {
+        double2 m[9];
+#pragma unroll
+        for (int j = 0; j < 9; ++j) m[j] = make_double2(w.e[j / 3][j % 3].re, w.e[j / 3][j % 3].im);
+        proj_iterate<WAVES>(m);
+#pragma unroll
+        for (int j = 0; j < 9; ++j) x.e[j / 3][j % 3] = {m[j].x, m[j].y};
+    }
     return x;
 }
 
@@ -501,73 +601,116 @@ __device__ __forceinline__ int fidx(int a, int b) { return a * 3 + (b < a ? b : 
 struct HypArgs {
     HypGeom g;
     const double2* U;  // natural [4][V][9] double2
-    double2* lv1;      // [12][9][V]
-    double2* lv2;      // [12][9][V]
+    char* up;          // the links, planes [4][9][V]
+    char* lv1;         // planes [12][6][V]
+    char* lv2;         // planes [12][6][V]
     double2* out;      // natural [4][V][9]
     double a1, a2, a3;
+    __device__ __forceinline__ size_t plane() const { return (size_t)g.V * sizeof(double2); }
+    __device__ __forceinline__ char* links(int mu) const { return up + 9 * mu * plane(); }
+    __device__ __forceinline__ char* level1(int a, int b) const { return lv1 + 6 * fidx(a, b) * plane(); }
+    __device__ __forceinline__ char* level2(int a, int b) const { return lv2 + 6 * fidx(a, b) * plane(); }
 };
 
-__device__ __forceinline__ LinkField nat(const HypArgs& a, const double2* base, int mu) {
-    return {base + (long)mu * a.g.V * 9, 9, 1};
-}
-__device__ __forceinline__ LinkField plane(const HypArgs& a, const double2* base, int f) {
-    return {base + (long)f * a.g.V * 9, 1, a.g.V};
-}
-
-__global__ __launch_bounds__(256) void k_hyp_level1(HypArgs a) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= a.g.V) return;
-    const int f = blockIdx.y, mu = f / 3, eta = other(mu, f % 3);
-    const LinkField Um = nat(a, a.U, mu);
-    M3 w = ld(Um, s);
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            w.e[i][j].re *= 1.0 - a.a3;
-            w.e[i][j].im *= 1.0 - a.a3;
-        }
-    add_staples(w, 0.5 * a.a3, a.g, nat(a, a.U, eta), Um, s, mu, eta);
-    st(a.lv1 + (long)f * a.g.V * 9, 1, a.g.V, s, proj_su3(w));
+constexpr int HYP_NT = 256;
+// Blocks take all output fields of one run of HYP_NT sites before the next run, and each XCD gets a contiguous range
+// of that order: the fields of a site share most of the links they read.
+struct Work {
+    int f, s, n;  // output field, first site and number of sites of the block
+};
+__device__ __forceinline__ Work work_of(const HypArgs& a, int nf) {
+    const int l = remap_block(blockIdx.x, gridDim.x), blk = l / nf;
+    return {l - blk * nf, blk * HYP_NT, min(HYP_NT, a.g.V - blk * HYP_NT)};
 }
 
-__global__ __launch_bounds__(256) void k_hyp_level2(HypArgs a) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= a.g.V) return;
-    const int f = blockIdx.y, mu = f / 3, nu = other(mu, f % 3);
-    M3 w = ld(nat(a, a.U, mu), s);
+// A block's links of one direction in the natural layout [V][9], moved between memory and registers through LDS so
+// that memory sees consecutive 16-byte words (a lane's own link is 144 bytes from the next lane's).
+struct Stage {
+    double2 w[HYP_NT * 9];
+};
+__device__ __forceinline__ M3 ld_nat(Stage& sm, const double2* p, const Work& wk) {
+    const int n = wk.n * 9;
+    const double2* src = p + (size_t)wk.s * 9;
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int j = 0; j < 9; ++j) {
+        const int i = j * HYP_NT + threadIdx.x;
+        if (i < n) sm.w[i] = src[i];
+    }
+    __syncthreads();
+    M3 m;
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            w.e[i][j].re *= 1.0 - a.a2;
-            w.e[i][j].im *= 1.0 - a.a2;
-        }
+    for (int j = 0; j < 9; ++j) {
+        const double2 v = sm.w[threadIdx.x * 9 + j];
+        m.e[j / 3][j % 3] = {v.x, v.y};
+    }
+    return m;
+}
+__device__ __forceinline__ void st_nat(Stage& sm, double2* p, const Work& wk, const M3& m) {
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 9; ++j) sm.w[threadIdx.x * 9 + j] = make_double2(m.e[j / 3][j % 3].re, m.e[j / 3][j % 3].im);
+    __syncthreads();
+    const int n = wk.n * 9;
+    double2* dst = p + (size_t)wk.s * 9;
+#pragma unroll
+    for (int j = 0; j < 9; ++j) {
+        const int i = j * HYP_NT + threadIdx.x;
+        if (i < n) dst[i] = sm.w[i];
+    }
+}
+
+// Natural links -> planes.
+__global__ __launch_bounds__(HYP_NT) void k_hyp_planes(HypArgs a) {
+    __shared__ Stage sm;
+    const Work wk = work_of(a, 4);
+    const M3 m = ld_nat(sm, a.U + (size_t)wk.f * a.g.V * 9, wk);
+    if ((int)threadIdx.x < wk.n) st<3>(a.links(wk.f), a.plane(), 16u * (wk.s + threadIdx.x), m);
+}
+
+__global__ __launch_bounds__(HYP_NT) void k_hyp_level1(HypArgs a) {
+    const Work wk = work_of(a, 12);
+    if ((int)threadIdx.x >= wk.n) return;
+    const int s = wk.s + threadIdx.x;
+    const int mu = wk.f / 3, eta = other(mu, wk.f % 3);
+    M3 w = ld<3>(a.links(mu), a.plane(), 16u * s);
+    scale(w, 1.0 - a.a3);
+    add_staples<3>(w, 0.5 * a.a3, a.plane(), a.links(eta), a.links(mu), 16u * s,
+                   hop(a.g, s, mu).f, hop(a.g, s, eta));
+    st<2>(a.level1(mu, eta), a.plane(), 16u * s, proj_su3<2>(w));
+}
+
+// Levels 2 and 3 at three waves per SIMD (168 registers, none spilled); level 1 spills there and runs at two.
+__global__ __launch_bounds__(HYP_NT, 3) void k_hyp_level2(HypArgs a) {
+    const Work wk = work_of(a, 12);
+    if ((int)threadIdx.x >= wk.n) return;
+    const int s = wk.s + threadIdx.x;
+    const int mu = wk.f / 3, nu = other(mu, wk.f % 3);
+    M3 w = ld<3>(a.links(mu), a.plane(), 16u * s);
+    const unsigned fm = hop(a.g, s, mu).f;
+    scale(w, 1.0 - a.a2);
+#pragma unroll 1
     for (int rho = 0; rho < 4; ++rho) {
         if (rho == mu || rho == nu) continue;
         const int sg = 6 - mu - nu - rho;
-        add_staples(w, 0.25 * a.a2, a.g, plane(a, a.lv1, fidx(rho, sg)), plane(a, a.lv1, fidx(mu, sg)), s, mu, rho);
+        add_staples<2>(w, 0.25 * a.a2, a.plane(), a.level1(rho, sg), a.level1(mu, sg), 16u * s, fm, hop(a.g, s, rho));
     }
-    st(a.lv2 + (long)f * a.g.V * 9, 1, a.g.V, s, proj_su3(w));
+    st<2>(a.level2(mu, nu), a.plane(), 16u * s, proj_su3<3>(w));
 }
 
-__global__ __launch_bounds__(256) void k_hyp_level3(HypArgs a) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= a.g.V) return;
-    const int mu = blockIdx.y;
-    M3 w = ld(nat(a, a.U, mu), s);
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            w.e[i][j].re *= 1.0 - a.a1;
-            w.e[i][j].im *= 1.0 - a.a1;
-        }
+__global__ __launch_bounds__(HYP_NT, 3) void k_hyp_level3(HypArgs a) {
+    __shared__ Stage sm;
+    const Work wk = work_of(a, 4);
+    const int mu = wk.f;
+    const int s = wk.s + min((int)threadIdx.x, wk.n - 1);  // lanes past the end compute the last site, unstored
+    M3 w = ld<3>(a.links(mu), a.plane(), 16u * s);
+    const unsigned fm = hop(a.g, s, mu).f;
+    scale(w, 1.0 - a.a1);
+#pragma unroll 1
     for (int nu = 0; nu < 4; ++nu) {
         if (nu == mu) continue;
-        add_staples(w, a.a1 / 6.0, a.g, plane(a, a.lv2, fidx(nu, mu)), plane(a, a.lv2, fidx(mu, nu)), s, mu, nu);
+        add_staples<2>(w, a.a1 / 6.0, a.plane(), a.level2(nu, mu), a.level2(mu, nu), 16u * s, fm, hop(a.g, s, nu));
     }
-    st(a.out + (long)mu * a.g.V * 9, 9, 1, s, proj_su3(w));
+    st_nat(sm, a.out + (size_t)mu * a.g.V * 9, wk, proj_su3<3>(w));
 }
 
 }  // namespace
@@ -586,20 +729,27 @@ hipError_t launch_hyp(const Geom& g, const double* links, const double alpha[3],
     a.g.stride[2] = g.X * g.Y;
     a.g.stride[3] = g.X * g.Y * g.Z;
     a.g.V = 2 * g.Vh;
+    for (int mu = 0; mu < 4; ++mu) {
+        a.g.by_L[mu] = div_by(a.g.L[mu]);
+        a.g.by_stride[mu] = div_by(a.g.stride[mu]);
+    }
     a.U = (const double2*)links;
-    a.lv1 = (double2*)ws;
-    a.lv2 = (double2*)ws + 12L * a.g.V * 9;
+    a.lv1 = (char*)ws;
+    a.lv2 = a.lv1 + 72 * (size_t)a.g.V * sizeof(double2);
+    a.up = a.lv2 + 72 * (size_t)a.g.V * sizeof(double2);  // 180 of the workspace's 216 planes in all
     a.out = (double2*)out;
     a.a1 = alpha[0];
     a.a2 = alpha[1];
     a.a3 = alpha[2];
-    const unsigned nb = (unsigned)blocks_for(a.g.V, 256);
-    hipLaunchKernelGGL(k_hyp_level1, dim3(nb, 12), dim3(256), 0, s, a);
+    const int nb = blocks_for(a.g.V, HYP_NT);
+    hipLaunchKernelGGL(k_hyp_planes, dim3(nb * 4), dim3(HYP_NT), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e) return e;
-    hipLaunchKernelGGL(k_hyp_level2, dim3(nb, 12), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_hyp_level1, dim3(nb * 12), dim3(HYP_NT), 0, s, a);
     if ((e = hipGetLastError())) return e;
-    hipLaunchKernelGGL(k_hyp_level3, dim3(nb, 4), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_hyp_level2, dim3(nb * 12), dim3(HYP_NT), 0, s, a);
+    if ((e = hipGetLastError())) return e;
+    hipLaunchKernelGGL(k_hyp_level3, dim3(nb * 4), dim3(HYP_NT), 0, s, a);
     return hipGetLastError();
 }
 

@@ -47,6 +47,17 @@ def test_hyp_matches_oracle(dims, kind, alpha):
     assert np.max(np.abs(V - ref)) <= 1e-12
 
 
+@pytest.mark.parametrize("dims,eps", [((2, 2, 2, 2), 0.3), ((2, 2, 2, 34), 0.7), ((6, 2, 14, 4), 0.05),
+                                      ((4, 6, 10, 2), 1.0)])
+def test_hyp_blocks_and_projection_branches(dims, eps):
+    """Lattices of less than a block of 256 sites, and of one block and a remainder; link fields whose projections take
+    the short series (eps 0.05), the long one and the iterations (eps 1). Each projection is within a few 1e-15 of the
+    oracle's and three levels of it follow one another, so 1e-12 holds with the same margin as on the other fields."""
+    announce(f"hyp dims={dims} eps={eps}")
+    U = li.near_identity_links(dims, eps, 454)
+    assert np.max(np.abs(_gpu_hyp(dims, U) - hyp.hyp_smear(dims, U))) <= 1e-12
+
+
 def test_largest_weights_on_haar_links_ill_conditioned_maximum():
     # weights (1, 1, 1) on Haar links give staple sums whose determinant phase sits at +-pi; there the
     # maximiser of Re tr(X^dag W) lies along a nearly flat direction and the SU(2)-subgroup sweeps converge
