@@ -7,19 +7,25 @@
 //
 // Two launches, or one fused:
 //  * k_npr_paths: one block per hypercube; the path average is built by the first-step recursion in LDS
-//    (U_mu(x) for a step +mu, U_mu(x - mu)^dag for a step -mu), one thread per row of a corner pair's matrix,
-//    the 256 matrices held there as nine planes, one per matrix element, with the pairs swizzled across LDS
-//    banks. Output
+//    (U_mu(x) for a step +mu, U_mu(x - mu)^dag for a step -mu) for one of each two opposite corner pairs, the other
+//    being its conjugate transpose, the 256 matrices held there as nine planes, one per matrix element, with the
+//    pairs swizzled across LDS banks. Output
 //    [nz][256][9] double2: a hypercube's 256 matrices are one contiguous 36 KB block, written and read
 //    whole.
 //  * k_npr_contract: one block per hypercube, one thread per (A, C). M_{AB} is nonzero only for
 //    B = A xor S xor F, where it is a sign, so each thread owns one term: it keeps U_{A,D} and U_{C,B}
 //    (D = C xor S2 xor F2) in registers for every field set; the hypercube's 192 field values of up to
-//    NPR_CHUNK field sets are staged in LDS together, and one block reduction gives their O_i(z).
+//    NPR_CHUNK field sets are staged in LDS together, and one block reduction gives their O_i(z). The 36 KB of path
+//    links come in through LDS in whole cache lines.
 //  * k_npr_fused: both in one block per hypercube; the path links stay in LDS (for a few field sets per call this
 //    saves the 36 KB per hypercube written by k_npr_paths and read back by k_npr_contract).
 // Every kernel takes its hypercubes in XCD-aware order (block b on XCD b % 8 gets one of a contiguous range), so
 // that neighbouring hypercubes, which share cache lines of the fields and links, meet in one L2.
+// What bounds them: at 20^3x64 with 4 field sets the fused kernel keeps the vector units 63% and LDS 52% busy at three
+// waves per SIMD (160 registers: two matrices a thread). Half the products and LDS reads of the path build, eight sums
+// in 10 + 4 exchanges instead of 96, and one address per thread for the staged fields took it from 501 to 334 us (0.69 GB
+// of links, fields and results would take 111 us); on 12^3x24 with 9 sets the path links went from 26 to 23 us and a
+// contraction from 95 to 53 us.
 // The signs come from the anticommutation relations: gamma_X gamma_Y = (-1)^s(X,Y) gamma_{X xor Y} with
 // s(X,Y) = #{mu > nu : X_mu = Y_nu = 1}, gamma_X^dag = (-1)^{n(n-1)/2} gamma_X for n = |X|, tr gamma_0 = 4.
 #include "sp_launch.h"
@@ -61,6 +67,19 @@ __device__ __forceinline__ void coarse_coords(const NprGeom& g, int z, int* c) {
     c[3] = z / g.Lc[2];
 }
 
+// Offset of corner X of a hypercube from its corner 0 in the lattice (no wrap: 2 z_mu + 1 < L_mu).
+__device__ __forceinline__ int corner_offset(const NprGeom& g, int X) {
+    return (X & 1) + g.L[0] * (((X >> 1) & 1) + g.L[1] * (((X >> 2) & 1) + g.L[2] * (X >> 3)));
+}
+
+// Lattice index of corner 0 of hypercube z.
+__device__ __forceinline__ int npr_base(const NprGeom& g, int z) {
+    int zc[4];
+    coarse_coords(g, z, zc);
+    const int c0[4] = {2 * zc[0], 2 * zc[1], 2 * zc[2], 2 * zc[3]};
+    return lex4(g, c0);
+}
+
 // The path area: element j (row j / 3, column j % 3) of the 256 path matrices as nine planes, pair (X, Y) at
 // ppos(X, Y) in each (sp_npr_layout.h).
 using Paths = double2[9][NPR_PLANE];
@@ -72,12 +91,13 @@ __device__ __forceinline__ void path_ld(const Paths& P, int X, int Y, C (&m)[3][
 }
 
 // The pairs at corner distance LEVEL (2, 3 or 4), each U_AD the average over the LEVEL directions mu in which A
-// and D differ of L(A -> A^mu) U_{A^mu, D} (see build_paths). The work is cut into items of NC columns of one row
-// of one pair (NC = 3: a row; NC = 1: one element), numbered with A fastest, so the 16 lanes of a quarter
-// wavefront share the corner difference, the row and the columns and differ in A: their reads of U_{A, A^mu}
-// and U_{A^mu, D} and their writes of U_{A, D} fall in distinct LDS banks (sp_npr_layout.h). Every lane takes
-// the set bits of its difference in increasing order, so all lanes run the same LEVEL steps and the products
-// are summed in the same order whatever the cut.
+// and D differ of L(A -> A^mu) U_{A^mu, D} (see build_paths). Of the pairs (A, D) and (D, A) the one whose A lacks the
+// lowest differing direction is formed, and the other is its conjugate transpose: half the products and, the kernels
+// being bound by LDS reads, half of those. The work is cut into items of NC columns of one row of one pair (NC = 3: a
+// row, 12 reads for 9 complex multiply-adds; NC = 1: one element, 6 for 3), numbered with the eight A of a corner
+// difference fastest: their reads of U_{A, A^mu} and U_{A^mu, D} and their writes fall in distinct LDS banks
+// (sp_npr_layout.h). Every lane takes the set bits of its difference in increasing order, so all lanes run the same
+// LEVEL steps and the products are summed in the same order whatever the cut.
 template <int LEVEL, int NC>
 __device__ __forceinline__ void path_level(Paths& P) {
     // the corner differences with LEVEL bits set, in increasing order, four bits each
@@ -85,8 +105,9 @@ __device__ __forceinline__ void path_level(Paths& P) {
     constexpr unsigned tab = LEVEL == 2 ? 0xCA9653u : LEVEL == 3 ? 0xEDB7u : 0xFu;
     constexpr int per = 9 / NC;  // items per pair
     const double w = 1.0 / LEVEL;
-    for (int it = threadIdx.x; it < 16 * nd * per; it += 256) {
-        const int A = it & 15, sub = (it >> 4) % per, diff = (tab >> (4 * ((it >> 4) / per))) & 15, D = A ^ diff;
+    for (int it = threadIdx.x; it < 8 * nd * per; it += 256) {
+        const int a8 = it & 7, sub = (it >> 3) % per, diff = (tab >> (4 * ((it >> 3) / per))) & 15;
+        const int low = diff & -diff, A = (a8 & (low - 1)) | ((a8 & ~(low - 1)) << 1), D = A ^ diff;
         const int i = sub * NC / 3, j0 = (sub * NC) % 3;
         C acc[NC];
 #pragma unroll
@@ -94,9 +115,8 @@ __device__ __forceinline__ void path_level(Paths& P) {
         int left = diff;
 #pragma unroll
         for (int k = 0; k < LEVEL; ++k) {
-            const int mu = __builtin_ctz(left);
-            left &= left - 1;
-            const int A1 = A ^ (1 << mu), ql = ppos(A, A1), qr = ppos(A1, D);
+            const int bit = left & -left, A1 = A ^ bit, ql = ppos(A, A1), qr = ppos(A1, D);
+            left ^= bit;
             C L[3];
 #pragma unroll
             for (int k2 = 0; k2 < 3; ++k2) L[k2] = {P[i * 3 + k2][ql].x, P[i * 3 + k2][ql].y};
@@ -108,9 +128,13 @@ __device__ __forceinline__ void path_level(Paths& P) {
                 acc[c] = cmac(cmac(cmac(acc[c], L[0], R0), L[1], R1), L[2], R2);
             }
         }
-        const int q = ppos(A, D);
+        const int q = ppos(A, D), qd = ppos(D, A);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) P[i * 3 + j0 + c][q] = make_double2(w * acc[c].re, w * acc[c].im);
+        for (int c = 0; c < NC; ++c) {
+            const C v = {w * acc[c].re, w * acc[c].im};
+            P[i * 3 + j0 + c][q] = make_double2(v.re, v.im);
+            P[(j0 + c) * 3 + i][qd] = make_double2(v.re, -v.im);
+        }
     }
     __syncthreads();
 }
@@ -120,19 +144,19 @@ __device__ __forceinline__ void path_level(Paths& P) {
 // L(A -> A^mu) U_{A^mu, D}, where L(A -> A^mu) = U_{A, A^mu} is U_mu(z_A) when A_mu = 0 and U_mu(z_A - mu)^dag
 // otherwise. Distance 0 is the identity and distance 1 the hypercube's 32 links and their conjugate transposes,
 // stored straight from memory; pairs at distance 2, 3, 4 follow in that order, so every U_{A^mu, D} and
-// U_{A, A^mu} a thread needs is complete one barrier earlier. Distances 2 and 4 are cut into single elements
-// (864 and 144 items over the 256 threads), distance 3 into rows (192 items), which keeps each level's longest
-// chain of products short. Ends with a barrier.
+// U_{A, A^mu} a thread needs is complete one barrier earlier. Distances 2 and 3 are cut into rows (144 and 96 items
+// over the 256 threads), distance 4 into single elements (72), the fastest of the cuts measured (all elements 3% slower,
+// all rows 1 to 2%). Ends with a barrier.
 __device__ __forceinline__ void build_paths(const NprGeom& g, const double2* __restrict__ U, int z, Paths& P) {
     const int t = threadIdx.x;
-    int zc[4];
-    coarse_coords(g, z, zc);
-    for (int e = t; e < 32 * 9; e += 256) {
-        const int l = e / 9, j = e % 9, mu = l >> 3, c8 = l & 7;
-        const int X = (c8 & ((1 << mu) - 1)) | ((c8 >> mu) << (mu + 1));  // bit mu = 0
-        int c[4];
-        for (int nu = 0; nu < 4; ++nu) c[nu] = 2 * zc[nu] + ((X >> nu) & 1);
-        const double2 v = U[((long)mu * g.V + lex4(g, c)) * 9 + j];
+    const int base = npr_base(g, z);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int e = t + 256 * k;
+        if (e >= 32 * 9) break;
+        const int l = e / 9, j = e - 9 * l, mu = l >> 3, low = (1 << mu) - 1, c8 = l & 7;
+        const int X = (c8 & low) | ((c8 & ~low) << 1);  // bit mu = 0
+        const double2 v = U[((long)mu * g.V + base + corner_offset(g, X)) * 9 + j];
         const int Y = X | (1 << mu);
         P[j][ppos(X, Y)] = v;                                          // step +mu from z_X
         P[(j % 3) * 3 + j / 3][ppos(Y, X)] = make_double2(v.x, -v.y);  // step -mu from z_Y: the dagger
@@ -141,7 +165,7 @@ __device__ __forceinline__ void build_paths(const NprGeom& g, const double2* __r
 #pragma unroll
         for (int j = 0; j < 9; ++j) P[j][ppos(t, t)] = make_double2(j % 4 == 0 ? 1.0 : 0.0, 0.0);
     __syncthreads();
-    path_level<2, 1>(P);
+    path_level<2, 3>(P);
     path_level<3, 3>(P);
     path_level<4, 1>(P);
 }
@@ -172,56 +196,86 @@ struct NprArgs {
 // Field sets per pass of the contraction: their field values are staged together, so a pass pays one load
 // latency, and one block reduction covers all of them.
 constexpr int NPR_CHUNK = 4;
-// The 192 field values per set and hypercube (4 fields x 16 corners x 3 colours) of a pass, over 256 threads.
-static_assert(NPR_CHUNK * 192 == 3 * 256, "a pass's field values are three per thread");
 
-// Offset of corner X of a hypercube from its corner 0 in the lattice (no wrap: 2 z_mu + 1 < L_mu).
-__device__ __forceinline__ int corner_offset(const NprGeom& g, int X) {
-    return (X & 1) + g.L[0] * (((X >> 1) & 1) + g.L[1] * (((X >> 2) & 1) + g.L[2] * (X >> 3)));
+// The field values of a pass starting at set i0: thread t < 192 holds element t (field, corner, colour) of each of its
+// sets, so that one address serves all of them. Loads are always issued: a set past the last one reads the last one
+// instead, and stage_put does not store it (loads under a branch would each wait for their data before the next).
+struct Staged {
+    double2 s0, s1, s2, s3;
+};
+__device__ __forceinline__ Staged stage_get(const NprArgs& a, int base, int i0) {
+    const int t = threadIdx.x < 192 ? threadIdx.x : 0;
+    const int fi = t / 48, r = t - 48 * fi, corner = r / 3, c = r - 3 * corner;
+    const double2* f = fi == 0 ? a.f[0] : fi == 1 ? a.f[1] : fi == 2 ? a.f[2] : a.f[3];
+    const long at = (long)(base + corner_offset(a.g, corner)) * 3 + c, set = 3L * a.g.V;
+    const int last = a.n - 1;
+    return {f[min(i0, last) * set + at], f[min(i0 + 1, last) * set + at], f[min(i0 + 2, last) * set + at],
+            f[min(i0 + 3, last) * set + at]};
 }
 
-// Field value q of this thread's share (element threadIdx.x + 256 q) of the pass starting at set i0. The load is
-// always issued: an element past the pass reads the pass's first element instead, and stage_put does not store
-// it (loads under a branch would each wait for their data before the next one).
-__device__ __forceinline__ double2 stage_get(const NprArgs& a, int base, int i0, int q) {
-    const int m = min(NPR_CHUNK, a.n - i0);
-    const int e0 = threadIdx.x + 256 * q, e = e0 < m * 192 ? e0 : 0;
-    const int s = e / 192, r0 = e % 192, fi = r0 / 48, r = r0 % 48, corner = r / 3, c = r % 3;
-    return a.f[fi][((long)(i0 + s) * a.g.V + base + corner_offset(a.g, corner)) * 3 + c];
+__device__ __forceinline__ void stage_put(const NprArgs& a, int i0, const Staged& v, double2 (*fs)[4][16][3]) {
+    if (threadIdx.x >= 192) return;
+    double2* const w = &fs[0][0][0][0] + threadIdx.x;
+    w[0] = v.s0;
+    if (i0 + 1 < a.n) w[192] = v.s1;
+    if (i0 + 2 < a.n) w[384] = v.s2;
+    if (i0 + 3 < a.n) w[576] = v.s3;
 }
 
-__device__ __forceinline__ void stage_put(const NprArgs& a, int i0, int q, double2 v, double2 (*fs)[4][16][3]) {
-    const int m = min(NPR_CHUNK, a.n - i0);
-    const int e = threadIdx.x + 256 * q;
-    if (e < m * 192) fs[e / 192][(e % 192) / 48][(e % 48) / 3][e % 3] = v;
+// y^T U x, y and x in LDS.
+__device__ __forceinline__ C bilinear(const double2 (&y)[3], const C (&U)[3][3], const double2 (&x)[3]) {
+    const C x0 = {x[0].x, x[0].y}, x1 = {x[1].x, x[1].y}, x2 = {x[2].x, x[2].y};
+    C b = {0.0, 0.0};
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+        b = cmac(b, {y[r].x, y[r].y}, cmac(cmac(cmac({0.0, 0.0}, U[r][0], x0), U[r][1], x1), U[r][2], x2));
+    return b;
 }
 
-// Lattice index of corner 0 of hypercube z.
-__device__ __forceinline__ int npr_base(const NprGeom& g, int z) {
-    int zc[4];
-    coarse_coords(g, z, zc);
-    const int c0[4] = {2 * zc[0], 2 * zc[1], 2 * zc[2], 2 * zc[3]};
-    return lex4(g, c0);
+// Sums of eight values per thread over the 256 threads of a block; thread q < 8 returns that of value q. Each of the
+// first three exchanges of a wavefront halves the values a lane carries (the lane keeps the half that its bit names),
+// so that it takes 10 exchanges where eight separate sums take 48; then three lanes' worth of bits are summed as one
+// value. Ends with a barrier.
+__device__ __forceinline__ double block_fold8(const double (&v)[8]) {
+    __shared__ double sm[4][8];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    double a[4], b[2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double keep = lane & 4 ? v[4 + k] : v[k], give = lane & 4 ? v[k] : v[4 + k];
+        a[k] = keep + __shfl_xor(give, 4, 64);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const double keep = lane & 2 ? a[2 + k] : a[k], give = lane & 2 ? a[k] : a[2 + k];
+        b[k] = keep + __shfl_xor(give, 2, 64);
+    }
+    double c = (lane & 1 ? b[1] : b[0]) + __shfl_xor(lane & 1 ? b[0] : b[1], 1, 64);
+    c += __shfl_xor(c, 8, 64);
+    c += __shfl_xor(c, 16, 64);
+    c += __shfl_xor(c, 32, 64);
+    if (lane < 8) sm[wid][lane] = c;
+    __syncthreads();
+    double t = 0.0;
+    if (threadIdx.x < 8) t = ((sm[0][lane] + sm[1][lane]) + sm[2][lane]) + sm[3][lane];
+    __syncthreads();
+    return t;
 }
+static_assert(NPR_CHUNK == 4, "block_fold8 sums the real and imaginary parts of four sets");
 
 // The contraction of hypercube z for every field set, by thread (A, C) of a block holding U_{A,D} and U_{C,B} in
-// registers; fs (LDS) stages the hypercube's field values of NPR_CHUNK field sets at a time. When staged, the
-// caller has put the first pass's values in fs already (loaded early, so that their latency overlaps other
-// work); otherwise, and for later passes, the values are copied one at a time as a pass starts
-// (register staging there, or prefetching across the arithmetic, raises the kernel's registers past three
-// waves per SIMD; staging ahead of the path-link loads of k_npr_contract made it slower).
+// registers; fs (LDS) stages the hypercube's field values of NPR_CHUNK field sets at a time. The caller has put the
+// first pass's values there, loaded early, so that their latency overlaps other work; those of later passes are
+// loaded as a pass starts (prefetching them across the arithmetic raises the kernel's registers past three waves per
+// SIMD).
 __device__ __forceinline__ void contract_sets(const NprArgs& a, int z, int base, const C (&uad)[3][3],
-                                              const C (&ucb)[3][3], double2 (*fs)[4][16][3], bool staged) {
+                                              const C (&ucb)[3][3], double2 (*fs)[4][16][3]) {
     const int A = threadIdx.x >> 4, Cc = threadIdx.x & 15;
     const int B = A ^ a.d1, D = Cc ^ a.d2;
     const double sgn = (((a.neg1 >> A) ^ (a.neg2 >> Cc)) & 1) ? -1.0 : 1.0;
     for (int i0 = 0; i0 < a.n; i0 += NPR_CHUNK) {
         const int m = min(NPR_CHUNK, a.n - i0);
-        if (i0 > 0 || !staged)
-            for (int e = threadIdx.x; e < m * 192; e += 256) {
-                const int s = e / 192, r0 = e % 192, fi = r0 / 48, r = r0 % 48, corner = r / 3, c = r % 3;
-                fs[s][fi][corner][c] = a.f[fi][((long)(i0 + s) * a.g.V + base + corner_offset(a.g, corner)) * 3 + c];
-            }
+        if (i0 > 0) stage_put(a, i0, stage_get(a, base, i0), fs);
         __syncthreads();
         double v[2 * NPR_CHUNK];
 #pragma unroll
@@ -229,51 +283,41 @@ __device__ __forceinline__ void contract_sets(const NprArgs& a, int z, int base,
             v[2 * s] = v[2 * s + 1] = 0.0;
             if (s >= m) continue;
             // chib1(A)^T U_AD chi4(D) and chib3(C)^T U_CB chi2(B)
-            C b1 = {0.0, 0.0}, b2 = {0.0, 0.0};
-#pragma unroll
-            for (int r = 0; r < 3; ++r) {
-                C s1 = {0.0, 0.0}, s2 = {0.0, 0.0};
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const double2 x4 = fs[s][3][D][c], x2 = fs[s][1][B][c];
-                    s1 = cmac(s1, uad[r][c], {x4.x, x4.y});
-                    s2 = cmac(s2, ucb[r][c], {x2.x, x2.y});
-                }
-                const double2 y1 = fs[s][0][A][r], y3 = fs[s][2][Cc][r];
-                b1 = cmac(b1, {y1.x, y1.y}, s1);
-                b2 = cmac(b2, {y3.x, y3.y}, s2);
-            }
+            const C b1 = bilinear(fs[s][0][A], uad, fs[s][3][D]), b2 = bilinear(fs[s][2][Cc], ucb, fs[s][1][B]);
             const C term = cmac({0.0, 0.0}, b1, b2);
             v[2 * s] = sgn * term.re;
             v[2 * s + 1] = sgn * term.im;
         }
-        block_sum<2 * NPR_CHUNK>(v);  // ends with a barrier, so the staged values can be replaced next
-        if (threadIdx.x == 0)
-#pragma unroll
-            for (int s = 0; s < NPR_CHUNK; ++s)
-                if (s < m) a.out[(long)(i0 + s) * a.g.nz + z] = make_double2(v[2 * s], v[2 * s + 1]);
+        const double tot = block_fold8(v);  // ends with a barrier, so the staged values can be replaced next
+        if (threadIdx.x < 2 * m) ((double*)a.out)[((long)(i0 + (threadIdx.x >> 1)) * a.g.nz + z) * 2 + (threadIdx.x & 1)] = tot;
     }
 }
 
-// From stored path links: thread (A, C) loads U_{A,D} and U_{C,B} from the hypercube's block.
+// From stored path links: the hypercube's contiguous 36 KB block comes in whole cache lines and goes through the path
+// area of LDS (a thread's own two matrices are scattered over it), which then becomes the field staging, as in
+// k_npr_fused.
 __global__ __launch_bounds__(256) void k_npr_contract(NprArgs a) {
     const int z = remap_block(blockIdx.x, gridDim.x);
     const int A = threadIdx.x >> 4, Cc = threadIdx.x & 15;
     const int B = A ^ a.d1, D = Cc ^ a.d2;
-    __shared__ double2 fs[NPR_CHUNK][4][16][3];  // the hypercube's field values of a pass
+    __shared__ Paths P;
     const int base = npr_base(a.g, z);
-    C uad[3][3], ucb[3][3];
+    const Staged f = stage_get(a, base, 0);
     const double2* blk = a.uad + (long)z * 256 * 9;
 #pragma unroll
-    for (int j = 0; j < 9; ++j) {
-        const double2 v = blk[(A * 16 + D) * 9 + j];
-        const double2 w = blk[(Cc * 16 + B) * 9 + j];
-        uad[j / 3][j % 3] = {v.x, v.y};
-        ucb[j / 3][j % 3] = {w.x, w.y};
+    for (int k = 0; k < 9; ++k) {
+        const int e = threadIdx.x + 256 * k, pair = e / 9, j = e - 9 * pair;
+        P[j][ppos(pair >> 4, pair & 15)] = blk[e];
     }
-    contract_sets(a, z, base, uad, ucb, fs, false);
+    __syncthreads();
+    C uad[3][3], ucb[3][3];
+    path_ld(P, A, D, uad);
+    path_ld(P, Cc, B, ucb);
+    __syncthreads();  // every thread has read its matrices
+    double2(*fs)[4][16][3] = (double2(*)[4][16][3])&P[0][0];
+    stage_put(a, 0, f, fs);
+    contract_sets(a, z, base, uad, ucb, fs);
 }
-
 // Fused: the hypercube's path links are built in LDS (as k_npr_paths does) and contracted at once, so the 36 KB
 // of path links per hypercube never travel to memory and back. The first pass's field values are loaded before
 // the paths are built; once every thread holds its two matrices the path area is reused for the field staging
@@ -285,17 +329,15 @@ __global__ __launch_bounds__(256) void k_npr_fused(NprArgs a, const double2* __r
     __shared__ Paths P;
     static_assert(sizeof(double2) * NPR_CHUNK * 4 * 16 * 3 <= sizeof(Paths), "staging fits the path area");
     const int base = npr_base(a.g, z);
-    const double2 f0 = stage_get(a, base, 0, 0), f1 = stage_get(a, base, 0, 1), f2 = stage_get(a, base, 0, 2);
+    const Staged f = stage_get(a, base, 0);
     build_paths(a.g, U, z, P);
     C uad[3][3], ucb[3][3];
     path_ld(P, A, D, uad);
     path_ld(P, Cc, B, ucb);
     __syncthreads();  // every thread has read its matrices: the path area becomes the field staging
     double2(*fs)[4][16][3] = (double2(*)[4][16][3])&P[0][0];
-    stage_put(a, 0, 0, f0, fs);
-    stage_put(a, 0, 1, f1, fs);
-    stage_put(a, 0, 2, f2, fs);
-    contract_sets(a, z, base, uad, ucb, fs, true);
+    stage_put(a, 0, f, fs);
+    contract_sets(a, z, base, uad, ucb, fs);
 }
 
 // Sign of M_{A, A xor S xor F} = (1/4) tr(gamma_A^dag gamma_S gamma_B gamma_F^dag), B = A xor S xor F.

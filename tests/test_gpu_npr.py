@@ -99,3 +99,15 @@ def test_npr_errors():
         sp.npr_contract(lat, uad, *f, (16, 0, 0, 0))
     with pytest.raises(sp.StagError):
         sp.npr_contract_links(lat, to_dev(li.haar_links(dims, 605)), *f, (0, 0, -1, 0))
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (2, 4, 6, 2)])
+def test_npr_opposite_pairs_are_conjugate_transposes(dims):
+    """One of U_AD and U_DA is formed and the other stored as its conjugate transpose: equal bit for bit, for every
+    corner pair (the oracle forms each by its own paths)."""
+    announce(f"npr opposite pairs dims={dims}")
+    U = li.near_identity_links(dims, 0.7, 631)
+    uad = sp.npr_path_links(sp.Lattice(dims), to_dev(U))
+    torch.cuda.synchronize()
+    assert torch.equal(uad, uad.permute(0, 2, 1, 4, 3).conj().resolve_conj())
+    assert np.max(np.abs(to_host(uad) - npr.path_links(dims, U).reshape(uad.shape))) <= 1e-14
