@@ -636,31 +636,75 @@ __device__ __forceinline__ Vec3<typename Real<VP>::T> dslash_site(const Geom g, 
 // ------------------------------------------------------------------------------------------------------
 // Reductions (FP64, fixed order: deterministic for a fixed launch shape)
 // ------------------------------------------------------------------------------------------------------
+__device__ __forceinline__ double make_f64(unsigned lo, unsigned hi) {
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// v moved across the lanes of each row of 16 by a DPP control (row_ror:n is 0x120 + n)
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+    const long long b = __double_as_longlong(v);
+    return make_f64((unsigned)__builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true),
+                    (unsigned)__builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true));
+}
+// The sum over the wavefront, in every lane. The exchanges are those of a butterfly over lane distances 32, 16, 8, 4, 2
+// and 1, in registers: permlane swaps for the first two; within a row of 16, once lanes n apart agree, rotating by n / 2
+// pairs the same lanes as the distance n / 2 does. Six shuffles of a double through LDS took about 800 cycles.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    unsigned lo = (unsigned)__double_as_longlong(v), hi = (unsigned)(__double_as_longlong(v) >> 32);
+    auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    v = make_f64(l[0], h[0]) + make_f64(l[1], h[1]);
+    lo = (unsigned)__double_as_longlong(v);
+    hi = (unsigned)(__double_as_longlong(v) >> 32);
+    l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = make_f64(l[0], h[0]) + make_f64(l[1], h[1]);
+    v += dpp_move<0x128>(v);
+    v += dpp_move<0x124>(v);
+    v += dpp_move<0x122>(v);
+    v += dpp_move<0x121>(v);
     return v;
 }
 
-// Sums NV values per thread across the block; results valid in thread 0. blockDim.x <= 1024.
+// The block's sums of NV values per thread, in every thread: each wavefront's sums go to sm, and after one barrier every
+// thread adds them as a butterfly over the wavefronts does. blockDim.x <= 1024; sm is the caller's, used once per launch.
 template <int NV>
-__device__ __forceinline__ void block_sum(double (&v)[NV]) {
-    __shared__ double sm[NV][16];
+struct BlockSums {
+    double w[NV][16];
+};
+template <int NV>
+__device__ __forceinline__ void block_sum_all(double (&v)[NV], BlockSums<NV>& sm) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
 #pragma unroll
     for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
     if (lane == 0) {
 #pragma unroll
-        for (int k = 0; k < NV; ++k) sm[k][wid] = v[k];
+        for (int k = 0; k < NV; ++k) sm.w[k][wid] = v[k];
     }
     __syncthreads();
-    if (wid == 0) {
 #pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            double a = lane < nw ? sm[k][lane] : 0.0;
-            v[k] = wave_sum(a);
+    for (int k = 0; k < NV; ++k) {
+        if (nw <= 4) {
+            const double* w = sm.w[k];
+            v[k] = nw == 1 ? w[0] : nw == 2 ? w[0] + w[1] : (w[0] + w[2]) + (w[1] + (nw == 4 ? w[3] : 0.0));
+        } else {
+            double t[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) t[i] = i < nw ? sm.w[k][i] : 0.0;
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1)
+#pragma unroll
+                for (int i = 0; i < off; ++i) t[i] += t[i + off];
+            v[k] = t[0];
         }
     }
+}
+
+// The same where only thread 0 needs the sums and the block may call it again (a barrier at the end).
+template <int NV>
+__device__ __forceinline__ void block_sum(double (&v)[NV]) {
+    __shared__ BlockSums<NV> sm;
+    block_sum_all(v, sm);
     __syncthreads();
 }
 
@@ -738,6 +782,25 @@ __device__ __forceinline__ void fin_update(SolverState* st, double rho_new, bool
     }
     st->beta = rho_new / st->rho;
     st->rho = rho_new;
+}
+
+// The outcome of fin_alpha and fin_update without the state's update: whether the iteration goes on, and its beta. The
+// fields they read are loaded together (state_in), before a launch's gathers, so that every thread can take the decision
+// itself once it has the sum rho_new, with no broadcast from one thread.
+struct StateIn {
+    double rho, stop2, floor2, rr_ru, delta2;
+    int flags, iter, max_iter, iter_last_ru, ru_every;
+};
+__device__ __forceinline__ StateIn state_in(const SolverState* st) {
+    return {st->rho, st->stop2, st->floor2, st->rr_ru, st->delta2, st->flags, st->iter, st->max_iter, st->iter_last_ru,
+            st->ru_every};
+}
+__device__ __forceinline__ bool goes_on(const StateIn& s, double pq, double rho_new, bool chunk_end) {
+    bool stop = (s.flags & (ST_DONE | ST_PENDING)) != 0;
+    stop |= !(pq > 0.0) || !isfinite(pq) || !isfinite(s.rho) || !isfinite(rho_new);
+    stop |= rho_new <= s.stop2 || s.iter + 1 >= s.max_iter || rho_new < s.floor2 * s.rr_ru;
+    if (chunk_end) stop |= (s.delta2 > 0.0 && rho_new < s.delta2 * s.rr_ru) || s.iter + 1 - s.iter_last_ru >= s.ru_every;
+    return !stop;
 }
 
 // After a true residual r (|r|^2 = rho_true, rp = Re<r, p> with the current direction p). init = 1 for the

@@ -195,7 +195,8 @@ __device__ __forceinline__ void strided_tail(double (&acc)[NV], const double (&v
 // First reduction stage: block totals of NV values per thread, stored by thread 0 as dst[gblk][NV].
 template <int NV>
 __device__ __forceinline__ void block_partials(double* dst, int gblk, double (&v)[NV]) {
-    block_sum<NV>(v);
+    __shared__ BlockSums<NV> sm;
+    block_sum_all<NV>(v, sm);
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int k = 0; k < NV; ++k) dst[(size_t)gblk * NV + k] = v[k];
@@ -250,7 +251,12 @@ __global__ __launch_bounds__(256) void k_dslash(D d, int p, int in_slot, int out
     double pre[2] = {0.0, 0.0};  // FUSED: this thread's share of the |D_oe p|^2 and |p|^2 partials
     double head[HEAD][2];
     const double* const psrc[2] = {G.partials, G.partials_p};
-    if constexpr (FUSED) strided_head<2>(pre, head, psrc, G.nblk);
+    double st_m2 = 0.0, st_rho = 0.0;
+    if constexpr (FUSED) {
+        strided_head<2>(pre, head, psrc, G.nblk);
+        st_m2 = h.st[0]->m2;
+        st_rho = h.st[0]->rho;
+    }
     const bool live = cb < g.Vh;
     Vec3<R> acc[N];
 #pragma unroll
@@ -295,20 +301,16 @@ __global__ __launch_bounds__(256) void k_dslash(D d, int p, int in_slot, int out
     }
     R alpha_blk = R(0);
     if constexpr (FUSED) {
-        __shared__ double a_sh;
+        __shared__ BlockSums<2> sm;
         strided_tail<2>(pre, head, G.nblk);
-        block_sum<2>(pre);
-        if (threadIdx.x == 0) {
-            const SolverState* st = h.st[0];
-            const double pq = st->m2 * pre[1] + pre[0];
-            a_sh = (pq > 0.0 && isfinite(pq)) ? st->rho / pq : 0.0;  // breakdown: no update, flagged later
-            if (gblk == 0) {
-                G.rec[0] = pq;
-                G.rec[1] = a_sh;
-            }
+        block_sum_all<2>(pre, sm);
+        const double pq = st_m2 * pre[1] + pre[0];
+        const double a = (pq > 0.0 && isfinite(pq)) ? st_rho / pq : 0.0;  // breakdown: no update, flagged later
+        if (threadIdx.x == 0 && gblk == 0) {
+            G.rec[0] = pq;
+            G.rec[1] = a;
         }
-        __syncthreads();
-        alpha_blk = (R)a_sh;
+        alpha_blk = (R)a;
     }
     if (live) {
         if constexpr (MODE == DS_PLAIN) {
@@ -344,7 +346,7 @@ __global__ __launch_bounds__(256) void k_dslash(D d, int p, int in_slot, int out
 #pragma unroll
                 for (int j = 0; j < NG; ++j) {
                     const int r = r0 + j;
-                    const R m2 = h.act[r] ? (R)h.st[r]->m2 : R(0);
+                    const R m2 = FUSED ? (R)st_m2 : h.act[r] ? (R)h.st[r]->m2 : R(0);
                     const R a = h.act[r] ? (FUSED ? alpha_blk : (R)h.st[r]->alpha) : R(0);
 #pragma unroll
                     for (int i = 0; i < 3; ++i) {
@@ -507,11 +509,7 @@ __global__ __launch_bounds__(256) void k_xpay(D d, int gate, int remap) {
             dots[r] = dd;
         }
     }
-    block_sum<N>(dots);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int r = 0; r < N; ++r) G.partials_p[(size_t)gblk * N + r] = dots[r];
-    }
+    block_partials<N>(G.partials_p, gblk, dots);
 }
 
 // One system, after DS_UPDATE_FUSED: every block sums the |r|^2 partials (same order in every block) and
@@ -527,7 +525,8 @@ __global__ __launch_bounds__(256) void k_xpay_fused(DescSingle d, SolverState* _
     using VF = VecFmt<VP>;
     const int gblk = logical_block(remap);
     const GroupDev& G = d.grp;
-    const SolverState* st = d.sys.st;
+    const StateIn si = state_in(d.sys.st);
+    const double pq = G.rec[0];
     const int Vh = G.g.Vh;
     const int cb = gblk * blockDim.x + threadIdx.x;
     const bool live = cb < Vh;
@@ -541,27 +540,24 @@ __global__ __launch_bounds__(256) void k_xpay_fused(DescSingle d, SolverState* _
         rv = VF::load(d.sys.v[S_R], Vh, cb);
         pv = VF::load(d.sys.v[S_P], Vh, cb);
     }
+    __shared__ BlockSums<1> sm;
     strided_tail<1>(part, head, G.nblk);
-    block_sum<1>(part);
-    __shared__ double beta_sh;
-    __shared__ int go_sh, ru_sh;
-    if (threadIdx.x == 0) {
-        SolverState s = *st;
-        bool go = false;
+    block_sum_all<1>(part, sm);
+    const bool go = goes_on(si, pq, part[0], chunk_end != 0);
+    if (gblk == 0 && threadIdx.x == 0) {
+        SolverState s = *d.sys.st;
         if (!(s.flags & (ST_DONE | ST_PENDING))) {
-            fin_alpha(&s, G.rec[0]);
+            fin_alpha(&s, pq);
             if (!(s.flags & ST_DONE)) fin_update(&s, part[0], chunk_end != 0);
-            go = !(s.flags & (ST_DONE | ST_PENDING));
             if (go) s.flags |= ST_T_STALE;  // p formed here: a following k_norm_rec applies D_oe to it
         }
-        if (gblk == 0) *st_out = s;
-        beta_sh = s.beta;
-        go_sh = go;
-        ru_sh = chunk_end != 0 && (s.flags & ST_PENDING) && !(s.flags & ST_DONE);
+        *st_out = s;
     }
-    __syncthreads();
     if constexpr (VP != F64) {
-        if (ru_sh) {
+        // paused with nothing wrong: a reliable update is due
+        const bool broken = !(pq > 0.0) || !isfinite(pq) || !isfinite(si.rho) || !isfinite(part[0]);
+        const bool pending = (si.flags & ST_PENDING) || (!go && !broken);
+        if (chunk_end != 0 && pending && !(si.flags & ST_DONE)) {
             // the reliable update that follows the chunk starts here: x64 += x_lo; x_lo = 0 (k_accum's step)
             if (live) {
                 Vec3<double> x = VecFmt<F64>::load(d.sys.v[S_X64], Vh, cb);
@@ -577,8 +573,8 @@ __global__ __launch_bounds__(256) void k_xpay_fused(DescSingle d, SolverState* _
             return;
         }
     }
-    if (!go_sh) return;  // paused or stopped: p and its partials stay as they are
-    const R beta = (R)beta_sh;
+    if (!go) return;  // paused or stopped: p and its partials stay as they are
+    const R beta = (R)(part[0] / si.rho);
     double dots[1] = {0.0};
     if (live) {
 #pragma unroll
@@ -610,16 +606,16 @@ __global__ __launch_bounds__(256) void k_norm_rec(DescSingle d, SolverState* __r
     const int gblk = logical_block(remap);
     const GroupDev& G = d.grp;
     const SysDev& S = d.sys;
-    const SolverState* st = S.st;
     const Geom g = G.g;
     const int cb = gblk * blockDim.x + threadIdx.x;
     const bool live = cb < g.Vh;
-    const int flags = st->flags;
-    if (flags & (ST_DONE | ST_PENDING)) {
-        if (gblk == 0 && threadIdx.x == 0) *st_out = *st;
+    const StateIn si = state_in(S.st);
+    const double pq = G.rec[0];
+    if (si.flags & (ST_DONE | ST_PENDING)) {
+        if (gblk == 0 && threadIdx.x == 0) *st_out = *S.st;
         return;
     }
-    const bool direct = (flags & ST_T_STALE) != 0;
+    const bool direct = (si.flags & ST_T_STALE) != 0;
     double part[1] = {0.0};
     double head[HEAD][1];
     const double* const psrc[1] = {G.partials_r};
@@ -633,29 +629,23 @@ __global__ __launch_bounds__(256) void k_norm_rec(DescSingle d, SolverState* __r
             pv = VF::load(S.v[S_P], g.Vh, cb);
         }
     }
-    __shared__ double beta_sh;
-    __shared__ int go_sh;
     if (!direct) {
+        __shared__ BlockSums<1> sm;
         strided_tail<1>(part, head, G.nblk);
-        block_sum<1>(part);
+        block_sum_all<1>(part, sm);
     }
-    if (threadIdx.x == 0) {
-        SolverState s = *st;
-        bool go = true;
+    if (gblk == 0 && threadIdx.x == 0) {
+        SolverState s = *S.st;
         if (direct) {
             s.flags &= ~ST_T_STALE;
         } else {
-            fin_alpha(&s, G.rec[0]);
+            fin_alpha(&s, pq);
             if (!(s.flags & ST_DONE)) fin_update(&s, part[0], false);
-            go = !(s.flags & (ST_DONE | ST_PENDING));
         }
-        if (gblk == 0) *st_out = s;
-        beta_sh = direct ? 0.0 : s.beta;
-        go_sh = go;
+        *st_out = s;
     }
-    __syncthreads();
-    if (!go_sh) return;  // paused or stopped: t, p and their partials stay as they are
-    const R beta = (R)beta_sh;
+    if (!direct && !goes_on(si, pq, part[0], false)) return;  // paused or stopped: t, p and their partials stay
+    const R beta = direct ? R(0) : (R)(part[0] / si.rho);
     double dots[2] = {0.0, 0.0};
     if (live) {
         Vec3<R> t = acc;
@@ -677,7 +667,8 @@ __global__ __launch_bounds__(256) void k_norm_rec(DescSingle d, SolverState* __r
         for (int i = 0; i < 3; ++i)
             dots[0] += (double)t.c[i].re * (double)ts.c[i].re + (double)t.c[i].im * (double)ts.c[i].im;
     }
-    block_sum<2>(dots);
+    __shared__ BlockSums<2> sm2;
+    block_sum_all<2>(dots, sm2);
     if (threadIdx.x == 0) {
         G.partials[gblk] = dots[0];
         if (!direct) G.partials_p[gblk] = dots[1];
@@ -770,31 +761,29 @@ __global__ __launch_bounds__(1024) void k_finalize(D d, int kind, int gate) {
             else if (kind == FIN_ALPHA) s[k] += G.partials_p[(size_t)b * N + (k - N)];
         }
     }
-    block_sum<2 * N>(s);
+    __shared__ BlockSums<2 * N> sm;
+    block_sum_all<2 * N>(s, sm);
     // thread r updates system r (the states are independent, their loads overlap)
-    __shared__ double tot[2 * N];
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < 2 * N; ++k) tot[k] = s[k];
-    }
-    __syncthreads();
-    const int r = threadIdx.x;
-    if (r >= N || r >= G.nrhs) return;
     bool act = false;
     SolverState* st = nullptr;
+    double u = 0.0, v = 0.0, x = 0.0, y = 0.0;
 #pragma unroll
     for (int q = 0; q < N; ++q)
-        if (q == r) {
+        if (q == (int)threadIdx.x) {
             act = h.act[q];
             st = h.st[q];
+            u = s[q];
+            v = s[N + q];
+            x = s[2 * q];
+            y = s[2 * q + 1];
         }
     if (!act) return;
-    if (kind == FIN_ALPHA) fin_alpha(st, st->m2 * tot[N + r] + tot[r]);
-    else if (kind == FIN_UPDATE || kind == FIN_UPDATE_END) fin_update(st, tot[r], kind == FIN_UPDATE_END);
+    if (kind == FIN_ALPHA) fin_alpha(st, st->m2 * v + u);
+    else if (kind == FIN_UPDATE || kind == FIN_UPDATE_END) fin_update(st, u, kind == FIN_UPDATE_END);
     else if (kind == FIN_NORM_B) {
-        st->bnorm2 = tot[r];
-        st->stop2 = st->tol2 * tot[r];
-    } else fin_resid(st, tot[2 * r], tot[2 * r + 1], kind == FIN_RESID_INIT);
+        st->bnorm2 = u;
+        st->stop2 = st->tol2 * u;
+    } else fin_resid(st, x, y, kind == FIN_RESID_INIT);
 }
 
 // ------------------------------------------------------------------------------------------------------
