@@ -314,10 +314,11 @@ int make_layout(int nsys, const sp_system* systems, const sp_cg_params* prm, int
         // link-load policy stay the tuned ones. Measured: FP16 links with 128-thread blocks (the plain operator's
         // tuned shape) took the 20^3x64 solve from 21.9 to 25.8 ms.
         if (n_rhs_max == 1 && blocks_for(G.g.Vh, 256) <= FUSED_PARTIALS * 256) L->cfg.nt = 256;
+        L->cfg.quad = n_rhs_max == 1 && quad_lanes(G.g.Vh, lp, rc, prm->inner);
     }
     int blk = 0;
     for (auto& G : L->groups) {
-        G.nblk = blocks_for(G.g.Vh, L->cfg.nt);
+        G.nblk = blocks_for(L->cfg.quad ? 4 * G.g.Vh : G.g.Vh, L->cfg.nt);
         G.blk0 = blk;
         blk += G.nblk;
     }
@@ -1002,6 +1003,14 @@ static int dslash_desc(const sp_geom* g, const sp_gauge* U, int prec, const void
     return SP_OK;
 }
 
+// The blocks of a stand-alone operator launch; where the operator takes four lanes per site the block size is 256 whatever
+// the table says.
+static int dslash_shape(int Vh, int lp, int recon, int prec, LaunchCfg* c) {
+    c->quad = quad_lanes(Vh, lp, recon, prec);
+    if (c->quad) c->nt = 256;
+    return blocks_for(c->quad ? 4 * Vh : Vh, c->nt);
+}
+
 int sp_dslash(const sp_geom* g, const sp_gauge* U, int prec, const void* in, void* out, int out_parity, void* stream) {
     Geom G;
     DescSingle d;
@@ -1013,7 +1022,7 @@ int sp_dslash(const sp_geom* g, const sp_gauge* U, int prec, const void* in, voi
         std::lock_guard<std::mutex> lock(g_mu);
         c = tuned_cfg(G, lp, recon, prec);
     }
-    const int nb = blocks_for(G.Vh, c.nt);
+    const int nb = dslash_shape(G.Vh, lp, recon, prec, &c);
     d.grp.nblk = nb;
     HIP_TRY(launch_dslash(d, nb, c, lp, recon, prec, out_parity, S_P, S_T, DS_PLAIN, G_NONE, prec == SP_F64,
                           (hipStream_t)stream));
@@ -1079,7 +1088,7 @@ int sp_tune_dslash(const sp_geom* g, const sp_gauge* U, int prec, void* in, void
     float best_t = 0, best4_t = 0;
     HIP_TRY(sweep(
         [&](LaunchCfg c) {
-            const int nb = blocks_for(G.Vh, c.nt);
+            const int nb = dslash_shape(G.Vh, lp, recon, prec, &c);
             d.grp.nblk = nb;
             return launch_dslash(d, nb, c, lp, recon, prec, 1, S_P, S_T, DS_PLAIN, G_NONE, use64, s);
         },

@@ -19,6 +19,12 @@ struct Cx {
     R re, im;
 };
 
+// a compile-time integer as an argument
+template <int K>
+struct Const {
+    static constexpr int value = K;
+};
+
 template <class R>
 struct Vec3 {
     Cx<R> c[3];
@@ -629,6 +635,63 @@ __device__ __forceinline__ Vec3<typename Real<VP>::T> dslash_site(const Geom g, 
     for (int i = 0; i < 3; ++i) {
         acc.c[i].re *= R(0.5);
         acc.c[i].im *= R(0.5);
+    }
+    return acc;
+}
+
+// ------------------------------------------------------------------------------------------------------
+// The half operator with four lanes per site, one direction each, for lattices whose sites alone leave the chip short of
+// wavefronts: a lane gathers one forward and one backward link and neighbour, all in flight at once, and the four
+// contributions are summed across the lanes. All four lanes of a site return its value, and must be active together.
+// ------------------------------------------------------------------------------------------------------
+// v summed over the four lanes of a quad, the same in every lane
+template <class R>
+__device__ __forceinline__ R quad_sum(R v) {
+    constexpr int X1 = 0xB1, X2 = 0x4E;  // quad_perm [1,0,3,2] and [2,3,0,1]
+    auto swap = [](R x, auto ctrl) {
+        constexpr int K = decltype(ctrl)::value;
+        if constexpr (sizeof(R) == 4) {
+            return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), K, 0xF, 0xF, true));
+        } else {
+            const long long b = __double_as_longlong(x);
+            const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)b, K, 0xF, 0xF, true);
+            const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(b >> 32), K, 0xF, 0xF, true);
+            return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+        }
+    };
+    v += swap(v, Const<X1>{});
+    v += swap(v, Const<X2>{});
+    return v;
+}
+
+template <int LP, int RECON, int VP>
+__device__ __forceinline__ Vec3<typename Real<VP>::T> dslash_quad(const Geom g, const void* links, const void* in, int p,
+                                                                  const Site s) {
+    using R = typename Real<VP>::T;
+    using LF = LinkFmt<LP, RECON>;
+    using VF = VecFmt<VP>;
+    const int mu = threadIdx.x & 3;
+    // as eta_sign and nbr, with the direction a lane's own
+    const int c = mu == 0 ? s.x : mu == 1 ? s.y : mu == 2 ? s.z : s.t;
+    const int L = mu == 0 ? g.X : mu == 1 ? g.Y : mu == 2 ? g.Z : g.T;
+    const int stride = g.Xh * (mu <= 1 ? 1 : mu == 2 ? g.Y : g.Y * g.Z);
+    const bool last = c == L - 1, first = c == 0;
+    const int ex = mu == 0 ? 0 : mu == 1 ? s.x : mu == 2 ? s.x + s.y : s.x + s.y + s.z;
+    const int nf = mu == 0 ? s.row + (last ? 0 : (c + 1) >> 1) : last ? s.cb - (L - 1) * stride : s.cb + stride;
+    const int nb = mu == 0 ? s.row + (first ? (L - 1) >> 1 : (c - 1) >> 1) : first ? s.cb + (L - 1) * stride : s.cb - stride;
+    const bool anti = mu == 3 && g.bc_t;
+    const bool negf = (ex & 1) != (anti && last), negb = (ex & 1) != (anti && first);
+    const Su3<R> Uf = LF::load(link_block<LF>(links, g.Vh, p, mu), g.Vh, s.cb);
+    const Vec3<R> vf = VF::load(in, g.Vh, nf);
+    const Su3<R> Ub = LF::load(link_block<LF>(links, g.Vh, 1 - p, mu), g.Vh, nb);
+    const Vec3<R> vb = VF::load(in, g.Vh, nb);
+    Vec3<R> acc = vzero<R>();
+    mv_acc(acc, Uf, vf, negf ? R(-0.5) : R(0.5));
+    mdv_acc(acc, Ub, vb, negb ? R(0.5) : R(-0.5));
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        acc.c[i].re = quad_sum(acc.c[i].re);
+        acc.c[i].im = quad_sum(acc.c[i].im);
     }
     return acc;
 }

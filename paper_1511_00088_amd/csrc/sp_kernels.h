@@ -214,14 +214,29 @@ __device__ __forceinline__ void block_partials(double* dst, int gblk, double (&v
 //              bit); the first partials are loaded before the gathers and summed after them. Saves the
 //              alpha finalize launch when the partials are few; |r|^2 partials go to partials_r, Re<p,Ap>
 //              and alpha to rec for k_xpay_fused, which takes the place of the update finalize.
+// POL (one system): how the operator gathers, see Policy.
 // ------------------------------------------------------------------------------------------------------
 enum DsMode : int { DS_PLAIN = 0, DS_NORM = 1, DS_UPDATE = 2, DS_UPDATE_FUSED = 3 };
+
+// How a single-system operator gathers: one lane per site with cached or streaming link loads, or four lanes per site
+// (cached), one direction each (dslash_quad); its blocks then cover blockDim.x / 4 sites, and lane 0 of each four does
+// the rest of the site's work.
+enum Policy : int { CACHED = 0, STREAM = 1, QUAD = 2 };
+template <int POL>
+__device__ __forceinline__ int site_index(int gblk) {
+    const int i = gblk * blockDim.x + threadIdx.x;
+    return POL == QUAD ? i >> 2 : i;
+}
+template <int POL>
+__device__ __forceinline__ bool site_lead() {
+    return POL != QUAD || (threadIdx.x & 3) == 0;
+}
 
 // Multi-system launches keep every load unconditional so that the compiler can keep all of them in flight:
 // right-hand sides beyond the group's count read the last system's vectors and store nothing, and systems
 // that are stopped or paused are computed with zero coefficients (x += 0 p, r -= 0 q, p = 0 r + 1 p leave
 // their stored values unchanged). Only temporaries (t) are overwritten for them.
-template <int LP, int RECON, int VP, int N, class D, int MODE, bool NT = false>
+template <int LP, int RECON, int VP, int N, class D, int MODE, int POL = CACHED>
 __global__ __launch_bounds__(256) void k_dslash(D d, int p, int in_slot, int out_slot, int gate, int use64,
                                                 int remap) {
     using R = typename Real<VP>::T;
@@ -242,7 +257,9 @@ __global__ __launch_bounds__(256) void k_dslash(D d, int p, int in_slot, int out
     const void* in[N];
 #pragma unroll
     for (int r = 0; r < N; ++r) in[r] = sys_of(d, G.sys0 + (r < nr ? r : nr - 1)).v[in_slot];
-    const int cb = gblk * blockDim.x + threadIdx.x;
+    constexpr bool NT = POL == STREAM;
+    static_assert(POL == CACHED || N == 1, "streaming and quad gathers are built for one system");
+    const int cb = site_index<POL>(gblk);
     double dots[N];
 #pragma unroll
     for (int r = 0; r < N; ++r) dots[r] = 0.0;
@@ -262,7 +279,9 @@ __global__ __launch_bounds__(256) void k_dslash(D d, int p, int in_slot, int out
 #pragma unroll
     for (int r = 0; r < N; ++r) acc[r] = vzero<R>();
 
-    if (live) {
+    if constexpr (POL == QUAD) {
+        if (live) acc[0] = dslash_quad<LP, RECON, VP>(g, links, in[0], p, site_of(g, p, cb));
+    } else if (live) {
         const Site s = site_of(g, p, cb);
 // several systems: two directions at a time (FP32 and 16-bit vectors; 105-158 VGPRs for four systems, 1% faster
 // batches than one at a time), one in FP64 (its four-system update holds 216 VGPRs already); one system: two at a time
@@ -312,7 +331,7 @@ __global__ __launch_bounds__(256) void k_dslash(D d, int p, int in_slot, int out
         }
         alpha_blk = (R)a;
     }
-    if (live) {
+    if (live && site_lead<POL>()) {
         if constexpr (MODE == DS_PLAIN) {
 #pragma unroll
             for (int r = 0; r < N; ++r)
@@ -384,7 +403,7 @@ __global__ __launch_bounds__(256) void k_dslash(D d, int p, int in_slot, int out
 // update, 1 the start of a solve from a given x0, 2 the start from x0 = 0, where r = b needs no operator (t64 is
 // then neither read nor needed).
 // ------------------------------------------------------------------------------------------------------
-template <int OP, int N, class D>
+template <int OP, int N, class D, int POL = CACHED>
 __global__ __launch_bounds__(256) void k_resid(D d, int init, int remap) {
     using LF = LinkFmt<F64, 18>;
     using VO = VecFmt<OP>;
@@ -396,7 +415,7 @@ __global__ __launch_bounds__(256) void k_resid(D d, int init, int remap) {
     const Rhs<N> h = rhs_of<N>(d, G, init ? G_ALIVE : G_RU);
     if (!h.any) return;
     const Geom g = G.g;
-    const int cb = gblk * blockDim.x + threadIdx.x;
+    const int cb = site_index<POL>(gblk);
     double dots[2 * N];
 #pragma unroll
     for (int r = 0; r < 2 * N; ++r) dots[r] = 0.0;
@@ -413,8 +432,19 @@ __global__ __launch_bounds__(256) void k_resid(D d, int init, int remap) {
         // two directions at a time for one system, as in the FP64 half operator (all four put the kernel past 256
         // registers, one wave per SIMD)
         constexpr int UNROLL = N == 1 ? 2 : 4;
+        if constexpr (POL == QUAD) {
+            static_assert(N == 1, "quad gathers are built for one system");
+            if (!zero_x) {
+                acc[0] = dslash_quad<F64, 18, F64>(g, G.links64, tin[0], 0, s);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    acc[0].c[i].re *= 2.0;
+                    acc[0].c[i].im *= 2.0;
+                }
+            }
+        }
 #pragma unroll UNROLL
-        for (int mu = 0; mu < (zero_x ? 0 : 4); ++mu) {
+        for (int mu = 0; mu < (zero_x || POL == QUAD ? 0 : 4); ++mu) {
             double e = (double)eta_sign(s, mu);
             double sf = e, sb = -e;
             if (mu == 3 && g.bc_t) {
@@ -434,7 +464,7 @@ __global__ __launch_bounds__(256) void k_resid(D d, int init, int remap) {
         }
 #pragma unroll
         for (int r = 0; r < N; ++r) {
-            if (!h.act[r]) continue;
+            if (!h.act[r] || !site_lead<POL>()) continue;
             const SysDev& S = sys_of(d, G.sys0 + r);
             const Vec3<double> b = VecFmt<F64>::load(S.v[S_B64], g.Vh, cb);
             const Vec3<double> x = zero_x ? vzero<double>() : VecFmt<F64>::load(S.v[S_X64], g.Vh, cb);
@@ -599,7 +629,7 @@ __global__ __launch_bounds__(256) void k_xpay_fused(DescSingle d, SolverState* _
 // state to st_out. When p was formed elsewhere (start, reliable update, end of the last chunk: ST_T_STALE)
 // the launch applies D_oe to p directly and takes no decision. Partials: Re<D_oe in, t> as DS_NORM, and
 // |p_i|^2 from the recurrence (the other paths leave the |p|^2 partials of the launch that formed p).
-template <int LP, int RECON, int VP, bool NT = false>
+template <int LP, int RECON, int VP, int POL = CACHED>
 __global__ __launch_bounds__(256) void k_norm_rec(DescSingle d, SolverState* __restrict__ st_out, int remap) {
     using R = typename Real<VP>::T;
     using VF = VecFmt<VP>;
@@ -607,8 +637,8 @@ __global__ __launch_bounds__(256) void k_norm_rec(DescSingle d, SolverState* __r
     const GroupDev& G = d.grp;
     const SysDev& S = d.sys;
     const Geom g = G.g;
-    const int cb = gblk * blockDim.x + threadIdx.x;
-    const bool live = cb < g.Vh;
+    const int cb = site_index<POL>(gblk);
+    const bool live = cb < g.Vh, lead = live && site_lead<POL>();
     const StateIn si = state_in(S.st);
     const double pq = G.rec[0];
     if (si.flags & (ST_DONE | ST_PENDING)) {
@@ -622,8 +652,10 @@ __global__ __launch_bounds__(256) void k_norm_rec(DescSingle d, SolverState* __r
     if (!direct) strided_head<1>(part, head, psrc, G.nblk);
     Vec3<R> acc = vzero<R>(), told = vzero<R>(), rv = vzero<R>(), pv = vzero<R>();
     if (live) {
-        acc = dslash_site<LP, RECON, VP, NT>(g, G.links_lo, direct ? S.v[S_P] : S.v[S_R], 1, site_of(g, 1, cb));
-        if (!direct) {
+        const void* in = direct ? S.v[S_P] : S.v[S_R];
+        if constexpr (POL == QUAD) acc = dslash_quad<LP, RECON, VP>(g, G.links_lo, in, 1, site_of(g, 1, cb));
+        else acc = dslash_site<LP, RECON, VP, POL == STREAM>(g, G.links_lo, in, 1, site_of(g, 1, cb));
+        if (!direct && lead) {
             told = VF::load(S.v[S_T], g.Vh, cb);
             rv = VF::load(S.v[S_R], g.Vh, cb);
             pv = VF::load(S.v[S_P], g.Vh, cb);
@@ -647,7 +679,7 @@ __global__ __launch_bounds__(256) void k_norm_rec(DescSingle d, SolverState* __r
     if (!direct && !goes_on(si, pq, part[0], false)) return;  // paused or stopped: t, p and their partials stay
     const R beta = direct ? R(0) : (R)(part[0] / si.rho);
     double dots[2] = {0.0, 0.0};
-    if (live) {
+    if (lead) {
         Vec3<R> t = acc;
         if (!direct) {
 #pragma unroll

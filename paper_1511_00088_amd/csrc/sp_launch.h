@@ -11,7 +11,22 @@ struct LaunchCfg {
     int nt = 256;    // threads per block (64, 128 or 256)
     int remap = 1;   // XCD-aware block order
     int stream = 0;  // link loads of the single-system half operator: 0 cached, 1 streaming (non-temporal)
+    int quad = 0;    // single-system half operator with four lanes per site (blocks of nt / 4 sites)
 };
+
+// Whether the single-system operator takes four lanes per site. Below about 30,000 sites per parity a lane per site leaves
+// the chip a few hundred wavefronts, each walking the directions in rounds of dependent latency. Measured per solve (tol
+// 1e-10, m = 0.05; four lanes against one, each with 256 threads): 2,048 sites 2.32 against 2.76 ms (FP32 recon 12),
+// 2.45 against 2.86 (recon 18) and 2.78 against 3.48 (FP64); 20,736 sites 3.22 against 3.59, 3.49 against 3.37 and 4.44
+// against 4.38; 32,768 sites 2.78 against 2.90 (recon 12) and 2.55 against 2.91 (fixed-point links); 65,536 sites 5.45
+// against 4.55 (recon 12), where the chip is full without it. FP32 recon 18 and FP64 move the most bytes a site and turn
+// first. FP16 and BF16 vectors keep a lane per site: the order of a site's eight terms decides how their last digits round,
+// and with it, by some percent either way, where such a solve's reliable updates fall.
+inline bool quad_lanes(int Vh, int lp, int recon, int vp) {
+    if (vp != F32 && vp != F64) return false;
+    const bool heavy = vp == F64 || (lp == F32 && recon == 18);
+    return Vh <= (heavy ? 8192 : 32768);
+}
 
 // Maximum systems per group in batched launches.
 static constexpr int NB = 4;

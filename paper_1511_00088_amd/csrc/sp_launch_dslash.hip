@@ -18,19 +18,19 @@ hipError_t launch_dslash(const D& d, int nblocks, LaunchCfg c, int lp, int recon
     constexpr int N = NOf<D>::value;
 // The streaming link loads are built for the single-system operator (N == 1) only; batched groups share each
 // link load among their right-hand sides and take the cached loads.
-#define SP_LAUNCH_NT(LP, RC, VP, NT)                                                                       \
+#define SP_LAUNCH_NT(LP, RC, VP, POL)                                                                      \
     do {                                                                                                   \
         if (mode == DS_PLAIN)                                                                              \
-            hipLaunchKernelGGL((k_dslash<LP, RC, VP, N, D, DS_PLAIN, NT>), dim3(nblocks), dim3(c.nt), 0, s, d, \
+            hipLaunchKernelGGL((k_dslash<LP, RC, VP, N, D, DS_PLAIN, POL>), dim3(nblocks), dim3(c.nt), 0, s, d, \
                                p, in_slot, out_slot, gate, use64, c.remap);                               \
         else if (mode == DS_NORM)                                                                          \
-            hipLaunchKernelGGL((k_dslash<LP, RC, VP, N, D, DS_NORM, NT>), dim3(nblocks), dim3(c.nt), 0, s, d, \
+            hipLaunchKernelGGL((k_dslash<LP, RC, VP, N, D, DS_NORM, POL>), dim3(nblocks), dim3(c.nt), 0, s, d, \
                                p, in_slot, out_slot, gate, use64, c.remap);                               \
         else if (mode == DS_UPDATE)                                                                        \
-            hipLaunchKernelGGL((k_dslash<LP, RC, VP, N, D, DS_UPDATE, NT>), dim3(nblocks), dim3(c.nt), 0, s, \
+            hipLaunchKernelGGL((k_dslash<LP, RC, VP, N, D, DS_UPDATE, POL>), dim3(nblocks), dim3(c.nt), 0, s, \
                                d, p, in_slot, out_slot, gate, use64, c.remap);                            \
         else if constexpr (N == 1)                                                                         \
-            hipLaunchKernelGGL((k_dslash<LP, RC, VP, N, D, DS_UPDATE_FUSED, NT>), dim3(nblocks), dim3(c.nt), 0, \
+            hipLaunchKernelGGL((k_dslash<LP, RC, VP, N, D, DS_UPDATE_FUSED, POL>), dim3(nblocks), dim3(c.nt), 0, \
                                s, d, p, in_slot, out_slot, gate, use64, c.remap);                         \
         else                                                                                               \
             return hipErrorInvalidValue;                                                                   \
@@ -39,9 +39,12 @@ hipError_t launch_dslash(const D& d, int nblocks, LaunchCfg c, int lp, int recon
 #define SP_LAUNCH(LP, RC, VP)                                                                              \
     do {                                                                                                   \
         if constexpr (N == 1) {                                                                            \
-            if (c.stream) SP_LAUNCH_NT(LP, RC, VP, true);                                                  \
+            if constexpr (VP == F32 || VP == F64) {                                                        \
+                if (c.quad) SP_LAUNCH_NT(LP, RC, VP, QUAD);                                                \
+            }                                                                                              \
+            if (c.stream) SP_LAUNCH_NT(LP, RC, VP, STREAM);                                                \
         }                                                                                                  \
-        SP_LAUNCH_NT(LP, RC, VP, false);                                                                   \
+        SP_LAUNCH_NT(LP, RC, VP, CACHED);                                                                   \
     } while (0)
     if (lp == F64 && recon == 18 && vp == F64) SP_LAUNCH(F64, 18, F64);
     if (lp == F32 && recon == 18 && vp == F32) SP_LAUNCH(F32, 18, F32);
@@ -67,11 +70,14 @@ hipError_t launch_norm_rec(const DescSingle& d, SolverState* st_out, int nblocks
                            hipStream_t s) {
 #define SP_LAUNCH(LP, RC, VP)                                                                              \
     do {                                                                                                   \
-        if (c.stream)                                                                                      \
-            hipLaunchKernelGGL((k_norm_rec<LP, RC, VP, true>), dim3(nblocks), dim3(c.nt), 0, s, d, st_out,  \
+        if (c.quad)                                                                                        \
+            hipLaunchKernelGGL((k_norm_rec<LP, RC, VP, QUAD>), dim3(nblocks), dim3(c.nt), 0, s, d, st_out,  \
+                               c.remap);                                                                   \
+        else if (c.stream)                                                                                 \
+            hipLaunchKernelGGL((k_norm_rec<LP, RC, VP, STREAM>), dim3(nblocks), dim3(c.nt), 0, s, d, st_out,  \
                                c.remap);                                                                   \
         else                                                                                               \
-            hipLaunchKernelGGL((k_norm_rec<LP, RC, VP, false>), dim3(nblocks), dim3(c.nt), 0, s, d, st_out, \
+            hipLaunchKernelGGL((k_norm_rec<LP, RC, VP, CACHED>), dim3(nblocks), dim3(c.nt), 0, s, d, st_out, \
                                c.remap);                                                                   \
         return hipGetLastError();                                                                          \
     } while (0)
@@ -94,6 +100,12 @@ hipError_t launch_resid(const D& d, int nblocks, LaunchCfg c, int op, int init, 
     constexpr int N = NOf<D>::value;
 #define SP_LAUNCH(OP)                                                                                      \
     do {                                                                                                   \
+        if constexpr (N == 1 && (OP == F32 || OP == F64)) {                                                \
+            if (c.quad) {                                                                                  \
+                hipLaunchKernelGGL((k_resid<OP, N, D, QUAD>), dim3(nblocks), dim3(c.nt), 0, s, d, init, c.remap); \
+                return hipGetLastError();                                                                  \
+            }                                                                                              \
+        }                                                                                                  \
         hipLaunchKernelGGL((k_resid<OP, N, D>), dim3(nblocks), dim3(c.nt), 0, s, d, init, c.remap);         \
         return hipGetLastError();                                                                          \
     } while (0)

@@ -44,6 +44,37 @@ def test_dslash_parity_small(prec, recon, dims, bc_t):
         assert err <= _tol(prec, recon), (prec, recon, p, err)
 
 
+@pytest.mark.parametrize("prec,recon,lp", [("f32", 18, "f32"), ("f64", 18, "f64"), ("f32", 12, "f32"),
+                                           ("f32", 12, "i16"), ("f32", 8, "f32")])
+@pytest.mark.parametrize("dims", [(8, 8, 16, 16), (10, 6, 14, 20), (16, 16, 16, 16), (12, 14, 20, 20)])
+def test_dslash_either_side_of_four_lanes_per_site(prec, recon, lp, dims):
+    """Volumes at and just past the limits up to which the operator takes four lanes per site: 8,192 sites per parity
+    (then 8,400) for FP32 recon 18 and FP64, 32,768 (then 33,600) for the other packings of FP32 vectors; antiperiodic time, both
+    parities, every site, at the gates of the small lattices."""
+    announce(f"dslash {prec} r{recon} links {lp} dims={dims}")
+    V = li.volume(dims)
+    U = li.near_identity_links(dims, 0.3, 111)
+    G = gauge(dims, U, lp, recon, 1)
+    for p in (0, 1):
+        xin = li.gaussian_vector(V // 2, 112 + p)
+        err = rel_err_max(to_host(sp.dslash(G, to_dev(xin), p, prec)), oracle.dslash_eo(dims, U, xin, p, bc_t=1))
+        assert err <= DSLASH_TOL["f16" if lp == "i16" else prec], err
+
+
+@pytest.mark.parametrize("inner,recon,dims", [("f32", 12, (16, 16, 16, 16)), ("f32", 12, (12, 14, 20, 20)),
+                                              ("f32", 18, (8, 8, 16, 16)), ("f64", 18, (10, 6, 14, 20))])
+def test_solve_either_side_of_four_lanes_per_site(inner, recon, dims):
+    """Solves at and past the same limits: the residual of the solution through the oracle's operator."""
+    announce(f"solve {inner} r{recon} dims={dims}")
+    U = li.near_identity_links(dims, 0.3, 113)
+    b = li.gaussian_even_source(dims, 114)
+    x, st = sp.cg_solve(gauge(dims, U, inner, recon, 1), 0.1, to_dev(b), tol=1e-10, inner=inner, workspace=sp.Workspace())
+    xh = to_host(x)
+    r = b - (0.01 * xh - oracle.dslash_eo(dims, U, oracle.dslash_eo(dims, U, xh, 1, bc_t=1), 0, bc_t=1))
+    # the library stops on its own FP64 residual; the oracle's differs from it by rounding, some 1e-15 of |A||x|
+    assert st.converged and np.linalg.norm(r) <= 1.001e-10 * np.linalg.norm(b)
+
+
 @pytest.mark.parametrize("prec,recon", COMBOS)
 def test_dslash_parity_cfg1_sampled(prec, recon):
     """20^3x64 near-identity links: sampled sites (random + the ragged tail + the lattice corners)."""
