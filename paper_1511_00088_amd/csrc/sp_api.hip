@@ -871,28 +871,13 @@ int force_check(const sp_geom* g, const sp_gauge* U, double mass, const double* 
     return SP_OK;
 }
 
-// The gradient's launches, with the scratch at base (force_scratch_bytes(G) bytes, 256-byte aligned): pack x
-// and lambda to FP64 planes, y_x = D_oe x and y_l = D_oe lambda, gamma and the force link by link, and the
-// two-stage reduction of dl/dm. Every scratch word is written before it is read. Asynchronous on s.
-int force_enqueue(const sp_geom* g, const Geom& G, const sp_gauge* U, double mass, const double* x_e,
-                  const double* lambda_e, double* gamma, double* force, double* grad_mass, char* base, hipStream_t s) {
+// The gradient's launches (launch_gradient), with the scratch at base (force_scratch_bytes(G) bytes, 256-byte aligned).
+// Every scratch word is written before it is read. Asynchronous on s.
+int force_enqueue(const Geom& G, const sp_gauge* U, double mass, const double* x_e, const double* lambda_e, double* gamma,
+                  double* force, double* grad_mass, char* base, hipStream_t s) {
     const size_t v = align256((size_t)G.Vh * 48);
-    void* xp = base;
-    void* lp = base + v;
-    void* yx = base + 2 * v;
-    void* yl = base + 3 * v;
-    double* partials = (double*)(base + 4 * v);
-    HIP_TRY(launch_pack_vec(G.Vh, x_e, SP_F64, xp, s));
-    HIP_TRY(launch_pack_vec(G.Vh, lambda_e, SP_F64, lp, s));
-    sp_gauge Ug = *U;
-    Ug.lo = U->f64;
-    Ug.lo_prec = SP_F64;
-    int rc = sp_dslash(g, &Ug, SP_F64, xp, yx, 1, s);
-    if (rc) return rc;
-    rc = sp_dslash(g, &Ug, SP_F64, lp, yl, 1, s);
-    if (rc) return rc;
-    HIP_TRY(launch_force(G, U->f64, xp, lp, yx, yl, gamma, force, s));
-    if (grad_mass) HIP_TRY(launch_mass_grad(G, mass, xp, lp, partials, grad_mass, s));
+    const GradScratch w = {base, base + v, base + 2 * v, base + 3 * v, (double*)(base + 4 * v)};
+    HIP_TRY(launch_gradient(G, U->f64, x_e, lambda_e, mass, w, gamma, force, grad_mass, s));
     return SP_OK;
 }
 
@@ -1250,7 +1235,7 @@ int sp_cg_force(const sp_geom* g, const sp_gauge* U, double mass, const double* 
     if (ws_bytes < sp_force_workspace_bytes(g)) return fail(SP_ERR_WORKSPACE, "workspace too small");
     if (((uintptr_t)ws) & 255) return fail(SP_ERR_INVALID_ARG, "workspace not 256-byte aligned");
     hipStream_t s = (hipStream_t)stream;
-    rc = sp::force_enqueue(g, G, U, mass, x_e, lambda_e, gamma, force, grad_mass, (char*)ws, s);
+    rc = sp::force_enqueue(G, U, mass, x_e, lambda_e, gamma, force, grad_mass, (char*)ws, s);
     if (rc) return rc;
     HIP_TRY(hipStreamSynchronize(s));
     return SP_OK;

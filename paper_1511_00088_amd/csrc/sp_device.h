@@ -664,6 +664,27 @@ __device__ __forceinline__ R quad_sum(R v) {
     return v;
 }
 
+// The two hops of a site in a direction that differs between lanes: neighbours, and whether eta and the antiperiodic
+// time boundary make each term negative (as eta_sign and nbr have it).
+struct Leg {
+    int nf, nb;
+    bool negf, negb;
+};
+__device__ __forceinline__ Leg leg_of(const Geom& g, const Site& s, int mu) {
+    const int c = mu == 0 ? s.x : mu == 1 ? s.y : mu == 2 ? s.z : s.t;
+    const int L = mu == 0 ? g.X : mu == 1 ? g.Y : mu == 2 ? g.Z : g.T;
+    const int stride = g.Xh * (mu <= 1 ? 1 : mu == 2 ? g.Y : g.Y * g.Z);
+    const bool last = c == L - 1, first = c == 0;
+    const int ex = mu == 0 ? 0 : mu == 1 ? s.x : mu == 2 ? s.x + s.y : s.x + s.y + s.z;
+    const bool anti = mu == 3 && g.bc_t;
+    Leg l;
+    l.nf = mu == 0 ? s.row + (last ? 0 : (c + 1) >> 1) : last ? s.cb - (L - 1) * stride : s.cb + stride;
+    l.nb = mu == 0 ? s.row + (first ? (L - 1) >> 1 : (c - 1) >> 1) : first ? s.cb + (L - 1) * stride : s.cb - stride;
+    l.negf = (ex & 1) != (anti && last);
+    l.negb = (ex & 1) != (anti && first);
+    return l;
+}
+
 template <int LP, int RECON, int VP>
 __device__ __forceinline__ Vec3<typename Real<VP>::T> dslash_quad(const Geom g, const void* links, const void* in, int p,
                                                                   const Site s) {
@@ -671,23 +692,14 @@ __device__ __forceinline__ Vec3<typename Real<VP>::T> dslash_quad(const Geom g, 
     using LF = LinkFmt<LP, RECON>;
     using VF = VecFmt<VP>;
     const int mu = threadIdx.x & 3;
-    // as eta_sign and nbr, with the direction a lane's own
-    const int c = mu == 0 ? s.x : mu == 1 ? s.y : mu == 2 ? s.z : s.t;
-    const int L = mu == 0 ? g.X : mu == 1 ? g.Y : mu == 2 ? g.Z : g.T;
-    const int stride = g.Xh * (mu <= 1 ? 1 : mu == 2 ? g.Y : g.Y * g.Z);
-    const bool last = c == L - 1, first = c == 0;
-    const int ex = mu == 0 ? 0 : mu == 1 ? s.x : mu == 2 ? s.x + s.y : s.x + s.y + s.z;
-    const int nf = mu == 0 ? s.row + (last ? 0 : (c + 1) >> 1) : last ? s.cb - (L - 1) * stride : s.cb + stride;
-    const int nb = mu == 0 ? s.row + (first ? (L - 1) >> 1 : (c - 1) >> 1) : first ? s.cb + (L - 1) * stride : s.cb - stride;
-    const bool anti = mu == 3 && g.bc_t;
-    const bool negf = (ex & 1) != (anti && last), negb = (ex & 1) != (anti && first);
+    const Leg l = leg_of(g, s, mu);
     const Su3<R> Uf = LF::load(link_block<LF>(links, g.Vh, p, mu), g.Vh, s.cb);
-    const Vec3<R> vf = VF::load(in, g.Vh, nf);
-    const Su3<R> Ub = LF::load(link_block<LF>(links, g.Vh, 1 - p, mu), g.Vh, nb);
-    const Vec3<R> vb = VF::load(in, g.Vh, nb);
+    const Vec3<R> vf = VF::load(in, g.Vh, l.nf);
+    const Su3<R> Ub = LF::load(link_block<LF>(links, g.Vh, 1 - p, mu), g.Vh, l.nb);
+    const Vec3<R> vb = VF::load(in, g.Vh, l.nb);
     Vec3<R> acc = vzero<R>();
-    mv_acc(acc, Uf, vf, negf ? R(-0.5) : R(0.5));
-    mdv_acc(acc, Ub, vb, negb ? R(0.5) : R(-0.5));
+    mv_acc(acc, Uf, vf, l.negf ? R(-0.5) : R(0.5));
+    mdv_acc(acc, Ub, vb, l.negb ? R(0.5) : R(-0.5));
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         acc.c[i].re = quad_sum(acc.c[i].re);

@@ -25,7 +25,7 @@ size_t force_scratch_bytes(const Geom& G);
 
 // Enqueues the gradient's launches on s with their scratch at base (256-byte aligned, force_scratch_bytes(G)
 // bytes); returns an sp_status.
-int force_enqueue(const sp_geom* g, const Geom& G, const sp_gauge* U, double mass, const double* x_e,
-                  const double* lambda_e, double* gamma, double* force, double* grad_mass, char* base, hipStream_t s);
+int force_enqueue(const Geom& G, const sp_gauge* U, double mass, const double* x_e, const double* lambda_e, double* gamma,
+                  double* force, double* grad_mass, char* base, hipStream_t s);
 
 }  // namespace sp

@@ -69,12 +69,14 @@ hipError_t launch_pack_vec(int Vh, const double* nat, int prec, void* out, hipSt
 hipError_t launch_unpack_vec(int Vh, const void* in, int prec, double* nat, hipStream_t s);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);  // bytes multiple of 16
 
-// Force: gamma / force in natural layout from packed FP64 x, lambda (even) and y_x, y_l (odd).
-hipError_t launch_force(const Geom& g, const void* links64, const void* x, const void* lam, const void* yx,
-                        const void* yl, double* gamma, double* force, hipStream_t s);
-// out = -2 m Re<lam, x> (device scalar), two-stage reduction through partials[mass_grad_blocks(g)].
-hipError_t launch_mass_grad(const Geom& g, double mass, const void* x, const void* lam, double* partials,
-                            double* out, hipStream_t s);
+// The gradient of sp_cg_force from natural x and lambda: three launches, with packed FP64 x, lambda (even), y_x and y_l
+// (odd) and mass_grad_blocks(g) partials of Re<lambda, x> as scratch. force and grad_mass may be null.
+struct GradScratch {
+    void *x, *lam, *yx, *yl;
+    double* partials;
+};
+hipError_t launch_gradient(const Geom& g, const void* links64, const double* x, const double* lam, double mass,
+                           const GradScratch& w, double* gamma, double* force, double* grad_mass, hipStream_t s);
 int mass_grad_blocks(const Geom& g);
 
 // Full-lattice solve helpers (sp_full.hip): split a natural full vector into packed FP64 halves, form

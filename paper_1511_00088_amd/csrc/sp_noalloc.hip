@@ -58,5 +58,5 @@ extern "C" int sp_cg_force_noalloc(const sp_geom* g, const sp_gauge* U, double m
     }
     char* base = nullptr;
     if ((rc = scratch_of_current_device(&base))) return rc;
-    return sp::force_enqueue(g, G, U, mass, x_e, lambda_e, gamma, force, grad_mass, base, (hipStream_t)stream);
+    return sp::force_enqueue(G, U, mass, x_e, lambda_e, gamma, force, grad_mass, base, (hipStream_t)stream);
 }
