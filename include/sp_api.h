@@ -161,6 +161,10 @@ size_t sp_gauge_bytes(const sp_geom* g, int prec, int recon);
  * checked here). */
 int sp_gauge_pack(const sp_geom* g, const double* links_nat, int prec, int recon, void* out, void* stream);
 
+/* The FP64 recon-18 packing (into f64) and a low-precision one (into lo; prec not SP_F64) of the same links in one pass,
+ * which reads them once: the two members of an sp_gauge, each as sp_gauge_pack writes it. Asynchronous on stream. */
+int sp_gauge_pack_both(const sp_geom* g, const double* links_nat, int prec, int recon, void* f64, void* lo, void* stream);
+
 /* Bytes of one packed parity-half vector of precision prec (FP16 includes a per-site FP32 norm). */
 size_t sp_vec_bytes(const sp_geom* g, int prec);
 

@@ -72,6 +72,7 @@ SIGNATURES = {
     "sp_last_error": (ctypes.c_char_p, []),
     "sp_gauge_bytes": (SZ, [PG, I, I]),
     "sp_gauge_pack": (I, [PG, P, I, I, P, P]),
+    "sp_gauge_pack_both": (I, [PG, P, I, I, P, P, P]),
     "sp_vec_bytes": (SZ, [PG, I]),
     "sp_vec_pack": (I, [PG, P, I, P, P]),
     "sp_vec_unpack": (I, [PG, P, I, P, P]),

@@ -89,16 +89,33 @@ def pack_gauge(lat: Lattice, links: torch.Tensor, prec, recon: int = 18) -> torc
     return out
 
 
+def _pack_gauge_both(lat: Lattice, links: torch.Tensor, prec: int, recon: int):
+    """The FP64 packing and one of precision prec, from one pass over the links."""
+    _check_c128(links, (4, lat.V, 3, 3), "links")
+    nbytes = lat.gauge_bytes(prec, recon)
+    if nbytes == 0:
+        raise ValueError(f"unsupported packing prec={prec} recon={recon}")
+    if recon == 8:
+        _refuse_recon8_singular(links)
+    f64 = torch.empty(lat.gauge_bytes(L.SP_F64, 18), dtype=torch.uint8, device=links.device)
+    lo = torch.empty(nbytes, dtype=torch.uint8, device=links.device)
+    L.check(L.load().sp_gauge_pack_both(ctypes.byref(lat.geom), _ptr(links), prec, recon, _ptr(f64), _ptr(lo), _stream()),
+            "sp_gauge_pack_both")
+    return f64, lo
+
+
 class Gauge:
     """A gauge field packed for the GPU: FP64 (recon 18) plus an optional low-precision packing (recon 18, 12, or
     8 for FP32 links)."""
 
     def __init__(self, lat: Lattice, links: torch.Tensor, lo_prec="f32", recon: int = 18):
         self.lat = lat
-        self.f64 = pack_gauge(lat, links, "f64", 18)
         self.lo_prec = _prec(lo_prec)
         self.recon = int(recon) if self.lo_prec != L.SP_F64 else 18
-        self.lo = self.f64 if self.lo_prec == L.SP_F64 else pack_gauge(lat, links, self.lo_prec, self.recon)
+        if self.lo_prec == L.SP_F64:
+            self.f64 = self.lo = pack_gauge(lat, links, "f64", 18)
+        else:
+            self.f64, self.lo = _pack_gauge_both(lat, links, self.lo_prec, self.recon)
         self.struct = L.sp_gauge(self.f64.data_ptr(), self.lo.data_ptr(), self.lo_prec, self.recon)
 
 

@@ -923,7 +923,19 @@ int sp_gauge_pack(const sp_geom* g, const double* links_nat, int prec, int recon
     if (!valid_link_prec(prec)) return fail(SP_ERR_INVALID_ARG, "bad precision %d", prec);
     if (link_bytes(prec, recon) == 0) return fail(SP_ERR_UNSUPPORTED, "precision %d with recon %d", prec, recon);
     if (!links_nat || !out) return fail(SP_ERR_INVALID_ARG, "null pointer");
-    HIP_TRY(launch_pack_gauge(G, links_nat, prec, recon, out, (hipStream_t)stream));
+    HIP_TRY(launch_pack_gauge(G, links_nat, prec, recon, out, nullptr, (hipStream_t)stream));
+    return SP_OK;
+}
+
+int sp_gauge_pack_both(const sp_geom* g, const double* links_nat, int prec, int recon, void* f64, void* lo, void* stream) {
+    Geom G;
+    int rc = check_geom(g, &G);
+    if (rc) return rc;
+    if (!valid_link_prec(prec)) return fail(SP_ERR_INVALID_ARG, "bad precision %d", prec);
+    if (prec == SP_F64 || link_bytes(prec, recon) == 0)
+        return fail(SP_ERR_UNSUPPORTED, "precision %d with recon %d beside FP64", prec, recon);
+    if (!links_nat || !f64 || !lo) return fail(SP_ERR_INVALID_ARG, "null pointer");
+    HIP_TRY(launch_pack_gauge(G, links_nat, prec, recon, lo, f64, (hipStream_t)stream));
     return SP_OK;
 }
 

@@ -363,10 +363,16 @@ struct LinkFmt<F64, 18> {
         }
         return U;
     }
+    template <bool NT = false>
     __device__ static void store(void* blk, int Vh, int cb, const double* r) {
-        double2* p = (double2*)blk;
+        typedef double v2 __attribute__((ext_vector_type(2)));
+        v2* p = (v2*)blk;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) p[(size_t)k * Vh + cb] = make_double2(r[2 * k], r[2 * k + 1]);
+        for (int k = 0; k < 9; ++k) {
+            const v2 v = {r[2 * k], r[2 * k + 1]};
+            if constexpr (NT) __builtin_nontemporal_store(v, p + (size_t)k * Vh + cb);
+            else p[(size_t)k * Vh + cb] = v;
+        }
     }
 };
 

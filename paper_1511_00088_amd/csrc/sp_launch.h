@@ -64,7 +64,7 @@ hipError_t launch_norm_rec(const DescSingle& d, SolverState* st_out, int nblocks
 template <class D>
 hipError_t launch_finalize(const D& d, int ngroups, int kind, int gate, hipStream_t s);
 
-hipError_t launch_pack_gauge(const Geom& g, const double* nat, int prec, int recon, void* out, hipStream_t s);
+hipError_t launch_pack_gauge(const Geom& g, const double* nat, int prec, int recon, void* out, void* f64, hipStream_t s);
 hipError_t launch_pack_vec(int Vh, const double* nat, int prec, void* out, hipStream_t s);
 hipError_t launch_unpack_vec(int Vh, const void* in, int prec, double* nat, hipStream_t s);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);  // bytes multiple of 16

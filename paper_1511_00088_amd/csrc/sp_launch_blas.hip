@@ -102,12 +102,11 @@ SP_INST(DescSingle)
 SP_INST(DescBatch)
 #undef SP_INST
 
-hipError_t launch_pack_gauge(const Geom& g, const double* nat, int prec, int recon, void* out, hipStream_t s) {
-    const long n = 8L * g.Vh;
-    const int nb = (int)((n + 255) / 256);
+hipError_t launch_pack_gauge(const Geom& g, const double* nat, int prec, int recon, void* out, void* f64, hipStream_t s) {
+    const dim3 nb(blocks_for(2 * g.Vh, 256), 4);
 #define SP_LAUNCH(P, RC)                                                                                   \
     do {                                                                                                   \
-        hipLaunchKernelGGL((k_pack_gauge<P, RC>), dim3(nb), dim3(256), 0, s, g, nat, out);                 \
+        hipLaunchKernelGGL((k_pack_gauge<P, RC>), nb, dim3(256), 0, s, g, (const double2*)nat, out, f64);   \
         return hipGetLastError();                                                                          \
     } while (0)
     if (prec == F64 && recon == 18) SP_LAUNCH(F64, 18);

@@ -194,3 +194,28 @@ def test_vector_packing_byte_for_byte(prec):
         got = packed.cpu().numpy()
         bad = np.nonzero(got != ref)[0]
         assert bad.size == 0, f"{prec}: {bad.size} bytes differ, first at {bad[:8]}"
+
+
+@pytest.mark.parametrize("prec,recon", [("f32", 18), ("f32", 12), ("f32", 8), ("f16", 12), ("bf16", 18), ("i16", 12)])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 6, 2, 8), (6, 4, 4, 4)])
+def test_both_packings_in_one_pass_equal_the_two_separate_ones(prec, recon, dims):
+    """A lattice of less than a block of 256 links a direction, one block and a remainder of 128 and of 128 of an odd
+    extent ratio: the two packings of a Gauge, byte for byte those of pack_gauge."""
+    announce(f"pack both {prec} r{recon} dims={dims}")
+    lat = sp.Lattice(dims)
+    U = to_dev(li.haar_links(dims, 815))
+    G = sp.Gauge(lat, U, lo_prec=prec, recon=recon)
+    assert torch.equal(G.f64, sp.pack_gauge(lat, U, "f64", 18))
+    assert torch.equal(G.lo, sp.pack_gauge(lat, U, prec, recon))
+
+
+def test_both_packings_refuse_what_the_single_one_refuses():
+    dims = (2, 2, 2, 2)
+    lat = sp.Lattice(dims)
+    U = to_dev(li.haar_links(dims, 816))
+    with pytest.raises(ValueError):
+        sp.Gauge(lat, U, lo_prec="f16", recon=8)
+    with pytest.raises(TypeError):
+        sp.Gauge(lat, U.to(torch.complex64), lo_prec="f32", recon=12)
+    with pytest.raises(ValueError):
+        sp.Gauge(lat, torch.zeros_like(U), lo_prec="f32", recon=8)
