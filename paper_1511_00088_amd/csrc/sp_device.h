@@ -676,12 +676,14 @@ struct Leg {
     int nf, nb;
     bool negf, negb;
 };
-__device__ __forceinline__ Leg leg_of(const Geom& g, const Site& s, int mu) {
-    const int c = mu == 0 ? s.x : mu == 1 ? s.y : mu == 2 ? s.z : s.t;
+// (the coordinates are copied first: a choice between members of s is one between their addresses, which puts s into LDS)
+__device__ __forceinline__ Leg leg_of(const Geom g, const Site s, int mu) {
+    const int x = s.x, y = s.y, z = s.z, t = s.t;
+    const int c = mu == 0 ? x : mu == 1 ? y : mu == 2 ? z : t;
     const int L = mu == 0 ? g.X : mu == 1 ? g.Y : mu == 2 ? g.Z : g.T;
     const int stride = g.Xh * (mu <= 1 ? 1 : mu == 2 ? g.Y : g.Y * g.Z);
     const bool last = c == L - 1, first = c == 0;
-    const int ex = mu == 0 ? 0 : mu == 1 ? s.x : mu == 2 ? s.x + s.y : s.x + s.y + s.z;
+    const int ex = mu == 0 ? 0 : mu == 1 ? x : mu == 2 ? x + y : x + y + z;
     const bool anti = mu == 3 && g.bc_t;
     Leg l;
     l.nf = mu == 0 ? s.row + (last ? 0 : (c + 1) >> 1) : last ? s.cb - (L - 1) * stride : s.cb + stride;
