@@ -179,22 +179,52 @@ std::string tune_key(const Geom& g, int lp, int recon, int vp) {
     return b;
 }
 
-LaunchCfg tuned_cfg(const Geom& g, int lp, int recon, int vp) {
-    auto it = g_tune.find(tune_key(g, lp, recon, vp));
-    return it == g_tune.end() ? LaunchCfg{} : it->second;
+// Launch shapes of lattices that the table does not hold, by size; measured on ten untuned lattices of 6,000 to 813,824
+// sites per parity.
+//  - The stand-alone operator: 64-thread blocks, which even out a last round of blocks (FP64 on 138,600 sites, two blocks
+//    of 256 a CU and a remainder: 31.4 against 35.7 us; never more than 3% slower). Links of 96 MB or more stream past the
+//    caches: a field of that size does not stay in the 256 MB Infinity Cache between two calls of a program that does
+//    anything else in between. Cold calls at 20^3x64: FP32 recon 12 (98 MB) 20.5 against 23.9 us, FP64 (295 MB) 56.7
+//    against 61.7; back to back on one field 18.9 against 17.9. Below, cached loads win cold too (recon 18 on 138,600
+//    sites, 80 MB: 15.1 against 15.5 us; fixed point on 331,776, 64 MB: 15.5 against 18.2).
+//  - A single solve, whose launches follow one another on one field: 256-thread blocks (the fused iteration's partials) and
+//    streaming only where the field exceeds the Infinity Cache by itself: at 225 MB (recon 12) 10.55 ms cached against
+//    11.98, at 290 (recon 18) 13.0 against 13.2, at 312 (recon 12) 16.8 against 16.3, at 382 (FP64) 16.9 against 15.7.
+//  - A batch: 64-thread blocks up to 40,000 sites (6,000 sites, three systems: 3.81 against 4.16 ms; 32,256: 4.23 against
+//    4.44), 256 beyond (63,360 sites, six systems: 6.09 against 6.19; 230,400: 16.4 against 16.7).
+size_t link_field_bytes(const Geom& g, int lp, int recon) { return 8 * (size_t)g.Vh * link_bytes(lp, recon); }
+
+bool find_cfg(const std::string& key, LaunchCfg* c) {
+    auto it = g_tune.find(key);
+    if (it != g_tune.end()) *c = it->second;
+    return it != g_tune.end();
 }
 
-// Launch shape of the NB-right-hand-side operator ("/n4" entry), else the single-system one.
+LaunchCfg tuned_cfg(const Geom& g, int lp, int recon, int vp) {
+    LaunchCfg c;
+    if (find_cfg(tune_key(g, lp, recon, vp), &c)) return c;
+    c.nt = 64;
+    c.stream = link_field_bytes(g, lp, recon) >= 96000000;
+    return c;
+}
+
+// Launch shape of the NB-right-hand-side operator ("/n4" entry), else the single-system one's.
 LaunchCfg tuned_cfg_batched(const Geom& g, int lp, int recon, int vp) {
-    auto it = g_tune.find(tune_key(g, lp, recon, vp) + "/n4");
-    return it == g_tune.end() ? tuned_cfg(g, lp, recon, vp) : it->second;
+    LaunchCfg c;
+    const std::string key = tune_key(g, lp, recon, vp);
+    if (find_cfg(key + "/n4", &c) || find_cfg(key, &c)) return c;
+    c.nt = g.Vh <= 40000 ? 64 : 256;
+    return c;
 }
 
 // Launch shape of a single solve's iteration ("/solve" entry: block order and link-load policy timed on the
 // solver's own launches, by the tuning driver), else the plain operator's.
 LaunchCfg tuned_cfg_solve(const Geom& g, int lp, int recon, int vp) {
-    auto it = g_tune.find(tune_key(g, lp, recon, vp) + "/solve");
-    return it == g_tune.end() ? tuned_cfg(g, lp, recon, vp) : it->second;
+    LaunchCfg c;
+    const std::string key = tune_key(g, lp, recon, vp);
+    if (find_cfg(key + "/solve", &c) || find_cfg(key, &c)) return c;
+    c.stream = link_field_bytes(g, lp, recon) >= 300000000;
+    return c;
 }
 
 // ---------------------------------------------------------------------------------------------------
