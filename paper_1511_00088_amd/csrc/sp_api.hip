@@ -268,7 +268,7 @@ struct GroupPlan {
     Geom g;
     const sp_gauge* U;
     std::vector<int> sys;  // indices into the caller's system list
-    int nblk = 0, blk0 = 0;
+    int nblk = 0, blk0 = 0, bundle = 1;
     size_t partials_off = 0, partials_p_off = 0, partials_r_off = 0, rec_off = 0;
 };
 
@@ -346,11 +346,32 @@ int make_layout(int nsys, const sp_system* systems, const sp_cg_params* prm, int
         if (n_rhs_max == 1 && blocks_for(G.g.Vh, 256) <= FUSED_PARTIALS * 256) L->cfg.nt = 256;
         L->cfg.quad = n_rhs_max == 1 && quad_lanes(G.g.Vh, lp, rc, prm->inner);
     }
+    // Groups of one gauge field stand in a row (bundles of up to BUNDLE) and share a first block: their blocks alternate.
+    auto same_field = [](const GroupPlan& a, const GroupPlan& b) {
+        return a.U->f64 == b.U->f64 && a.U->lo == b.U->lo && a.U->recon == b.U->recon && a.U->lo_prec == b.U->lo_prec &&
+               !memcmp(&a.g, &b.g, sizeof a.g);
+    };
+    for (size_t i = 0; i < L->groups.size(); ++i) {
+        size_t at = i + 1;
+        for (size_t k = i + 1; k < L->groups.size(); ++k)
+            if (same_field(L->groups[i], L->groups[k])) {
+                std::rotate(L->groups.begin() + at, L->groups.begin() + k, L->groups.begin() + k + 1);
+                ++at;
+            }
+        i = at - 1;
+    }
     int blk = 0;
-    for (auto& G : L->groups) {
-        G.nblk = blocks_for(L->cfg.quad ? 4 * G.g.Vh : G.g.Vh, L->cfg.nt);
-        G.blk0 = blk;
-        blk += G.nblk;
+    for (size_t i = 0; i < L->groups.size();) {
+        size_t n = 1;
+        while (n < BUNDLE && i + n < L->groups.size() && same_field(L->groups[i], L->groups[i + n])) ++n;
+        for (size_t k = i; k < i + n; ++k) {
+            GroupPlan& G = L->groups[k];
+            G.nblk = blocks_for(L->cfg.quad ? 4 * G.g.Vh : G.g.Vh, L->cfg.nt);
+            G.blk0 = blk;
+            G.bundle = (int)n;
+        }
+        blk += (int)n * L->groups[i].nblk;
+        i += n;
     }
     L->total_blocks = blk;
     // control block: states, descriptors
@@ -696,6 +717,7 @@ int solve_impl(int nsys, const sp_system* systems, const sp_cg_params* prm, sp_c
         gd.sys0 = sys_counter;
         gd.blk0 = G.blk0;
         gd.nblk = G.nblk;
+        gd.bundle = G.bundle;
         hg[k] = gd;
         for (int i : G.sys) {
             size_t so[NSLOT];
@@ -1133,6 +1155,7 @@ int sp_tune_dslash(const sp_geom* g, const sp_gauge* U, int prec, void* in, void
         hg.links_lo = d.grp.links_lo;
         hg.links64 = d.grp.links64;
         hg.nrhs = NB;
+        hg.bundle = 1;
         SysDev hs[NB] = {};
         hipError_t e = hipSuccess;
         for (int r = 0; r < NB && !e; ++r) {

@@ -44,6 +44,7 @@ struct GroupDev {
     double* partials_r; // [nblk]      block partials of |r|^2 from DS_UPDATE_FUSED
     double* rec;        // [2]         Re<p,Ap> and alpha of the last DS_UPDATE_FUSED (block 0 writes them)
     int nrhs, sys0, blk0, nblk;
+    int bundle;         // groups whose blocks alternate (same links and geometry, same blk0), this one among them
 };
 
 struct DescSingle {
@@ -58,18 +59,25 @@ struct DescBatch {
 };
 
 // --- descriptor access ---------------------------------------------------------------------------------
-__device__ __forceinline__ int find_group(const DescSingle&, int) { return 0; }
-// The group of a logical block: the number of groups that start at or before it, minus one (group starts
-// increase strictly). Lane l tests group l (then l + 64, ...), so the starts load in parallel instead of
-// one after the other. Called by whole waves at kernel entry.
-__device__ __forceinline__ int find_group(const DescBatch& d, int lblk) {
+// The group of a logical block, and the block's number in it.
+struct BlockOf {
+    int grp, blk;
+};
+__device__ __forceinline__ BlockOf block_of(const DescSingle&, int lblk) { return {0, lblk}; }
+// The groups that start at or before the block, counted: lane l tests group l (then l + 64, ...), so the starts load in
+// parallel instead of one after the other (starts do not decrease). The last of them closes the block's bundle, whose
+// groups take the blocks in turn: neighbouring blocks then read the same links at about the same time and on one XCD, whose
+// L2 serves all but the first of them. Called by whole waves at kernel entry.
+__device__ __forceinline__ BlockOf block_of(const DescBatch& d, int lblk) {
     int count = 0;
     for (int g0 = 0; g0 < d.ngroups; g0 += 64) {
         const int g = g0 + (int)(threadIdx.x & 63);
         const bool started = g < d.ngroups && d.grp[g].blk0 <= lblk;
         count += __popcll(__ballot(started));
     }
-    return __builtin_amdgcn_readfirstlane(count - 1);
+    const int last = __builtin_amdgcn_readfirstlane(count - 1);
+    const int k = d.grp[last].bundle, rel = lblk - d.grp[last].blk0, blk = rel / k;
+    return {last - (k - 1) + (rel - blk * k), blk};
 }
 __device__ __forceinline__ const GroupDev& grp_of(const DescSingle& d, int) { return d.grp; }
 __device__ __forceinline__ const GroupDev& grp_of(const DescBatch& d, int g) { return d.grp[g]; }
@@ -246,9 +254,9 @@ __global__ __launch_bounds__(256) void k_dslash(D d, int p, int in_slot, int out
     using RX = typename Real<XP>::T;
     using XF = VecFmt<XP>;
     const int lblk = logical_block(remap);
-    const int gi = find_group(d, lblk);
-    const GroupDev& G = grp_of(d, gi);
-    const int gblk = lblk - G.blk0;
+    const BlockOf bo = block_of(d, lblk);
+    const GroupDev& G = grp_of(d, bo.grp);
+    const int gblk = bo.blk;
     const Rhs<N> h = rhs_of<N>(d, G, gate);
     if (!h.any) return;
     const Geom g = G.g;
@@ -409,9 +417,9 @@ __global__ __launch_bounds__(256) void k_resid(D d, int init, int remap) {
     using VO = VecFmt<OP>;
     using RO = typename Real<OP>::T;
     const int lblk = logical_block(remap);
-    const int gi = find_group(d, lblk);
-    const GroupDev& G = grp_of(d, gi);
-    const int gblk = lblk - G.blk0;
+    const BlockOf bo = block_of(d, lblk);
+    const GroupDev& G = grp_of(d, bo.grp);
+    const int gblk = bo.blk;
     const Rhs<N> h = rhs_of<N>(d, G, init ? G_ALIVE : G_RU);
     if (!h.any) return;
     const Geom g = G.g;
@@ -496,9 +504,9 @@ __global__ __launch_bounds__(256) void k_xpay(D d, int gate, int remap) {
     using R = typename Real<VP>::T;
     using VF = VecFmt<VP>;
     const int lblk = logical_block(remap);
-    const int gi = find_group(d, lblk);
-    const GroupDev& G = grp_of(d, gi);
-    const int gblk = lblk - G.blk0;
+    const BlockOf bo = block_of(d, lblk);
+    const GroupDev& G = grp_of(d, bo.grp);
+    const int gblk = bo.blk;
     const Rhs<N> h = rhs_of<N>(d, G, gate);
     if (!h.any) return;
     const int Vh = G.g.Vh;
@@ -711,9 +719,9 @@ __global__ __launch_bounds__(256) void k_norm_rec(DescSingle d, SolverState* __r
 template <int N, class D>
 __global__ __launch_bounds__(256) void k_accum(D d, int remap) {
     const int lblk = logical_block(remap);
-    const int gi = find_group(d, lblk);
-    const GroupDev& G = grp_of(d, gi);
-    const int gblk = lblk - G.blk0;
+    const BlockOf bo = block_of(d, lblk);
+    const GroupDev& G = grp_of(d, bo.grp);
+    const int gblk = bo.blk;
     const Rhs<N> h = rhs_of<N>(d, G, G_RU);
     if (!h.any) return;
     const int Vh = G.g.Vh;
@@ -739,9 +747,9 @@ __global__ __launch_bounds__(256) void k_accum(D d, int remap) {
 template <int N, class D>
 __global__ __launch_bounds__(256) void k_norm_b(D d, int remap) {
     const int lblk = logical_block(remap);
-    const int gi = find_group(d, lblk);
-    const GroupDev& G = grp_of(d, gi);
-    const int gblk = lblk - G.blk0;
+    const BlockOf bo = block_of(d, lblk);
+    const GroupDev& G = grp_of(d, bo.grp);
+    const int gblk = bo.blk;
     const Rhs<N> h = rhs_of<N>(d, G, G_ALIVE);
     if (!h.any) return;
     const int Vh = G.g.Vh;

@@ -31,6 +31,12 @@ inline bool quad_lanes(int Vh, int lp, int recon, int vp) {
 // Maximum systems per group in batched launches.
 static constexpr int NB = 4;
 
+// Groups of one gauge field whose blocks alternate in batched launches, so that a link one of them has brought into an
+// XCD's L2 serves the others. Measured (bit-identical solutions; alternating 1, 2 and 4 groups): 16 systems on 16^3x32
+// 22.5, 19.6 and 18.7 ms, 12 on 24^3x48 79.1, 77.4 and 73.4, 16 on 20^3x64 93.9, 90.4 and 89.5; the 32-system workload
+// 224, 215 and 215.
+static constexpr size_t BUNDLE = 4;
+
 inline int blocks_for(int n, int nt) { return (n + nt - 1) / nt; }
 
 // The fused single-system iteration has every block sum all block partials of the previous launch (in the same

@@ -302,3 +302,31 @@ def test_batched_workload_32_systems_vs_oracle():
 def _true_resid_oracle(dims, U, m, b, x):
     r = b - oracle.apply_A(dims, U, m, x)
     return float(np.linalg.norm(r) / np.linalg.norm(b))
+
+
+@pytest.mark.parametrize("na,nb", [(9, 5), (17, 1), (4, 8), (21, 6)])
+def test_alternating_groups_of_a_field_change_nothing(na, nb):
+    """Systems of two fields listed in turn: field A's make up to six groups (bundles of four and the rest, the last group
+    not full), field B's lattice is smaller. Every solution equals, bit for bit, the one of a batch of its own field alone
+    (the launch shape is that of the larger lattice in both; field B is compared at that shape through the oracle)."""
+    announce(f"bundles of {na} and {nb} systems")
+    da, db = (6, 4, 8, 10), (4, 4, 4, 6)
+    UA, UB = li.near_identity_links(da, 0.3, 471), li.near_identity_links(db, 0.3, 472)
+    GA, GB = gauge(da, UA, "f32", 12), gauge(db, UB, "f32", 12)
+    ba = [to_dev(li.gaussian_even_source(da, 4710 + k)) for k in range(na)]
+    bb = [to_dev(li.gaussian_even_source(db, 4810 + k)) for k in range(nb)]
+    both, where = [], []
+    for k in range(max(na, nb)):
+        for f, (G, bs) in enumerate(((GA, ba), (GB, bb))):
+            if k < len(bs):
+                both.append((G, 0.05 + 0.01 * k, bs[k]))
+                where.append((f, k))
+    xs, st = sp.cg_solve_batched(both, tol=1e-9, workspace=sp.Workspace())
+    xa, _ = sp.cg_solve_batched([(GA, 0.05 + 0.01 * k, b) for k, b in enumerate(ba)], tol=1e-9, workspace=sp.Workspace())
+    assert all(s.converged for s in st)
+    for x, (f, k) in zip(xs, where):
+        if f == 0:
+            assert torch.equal(x, xa[k]), k
+        else:
+            ref = oracle.cg_solve(db, UB, 0.05 + 0.01 * k, to_host(bb[k]), tol=1e-12)[0]
+            assert rel_err_2(to_host(x), ref) <= 1e-6
