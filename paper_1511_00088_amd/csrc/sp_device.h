@@ -749,6 +749,24 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// The sums of a and b over the wavefront, each added in wave_sum's order: that of a in lanes 0 to 31, of b in 32 to 63.
+// The first exchange puts the halves of both into one register, so that two sums take the six steps of one.
+__device__ __forceinline__ double wave_sum2(double a, double b) {
+    const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+    auto l = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
+    auto h = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+    double v = make_f64(l[0], h[0]) + make_f64(l[1], h[1]);
+    const unsigned lo = (unsigned)__double_as_longlong(v), hi = (unsigned)(__double_as_longlong(v) >> 32);
+    l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = make_f64(l[0], h[0]) + make_f64(l[1], h[1]);
+    v += dpp_move<0x128>(v);
+    v += dpp_move<0x124>(v);
+    v += dpp_move<0x122>(v);
+    v += dpp_move<0x121>(v);
+    return v;
+}
+
 // The block's sums of NV values per thread, in every thread: each wavefront's sums go to sm, and after one barrier every
 // thread adds them as a butterfly over the wavefronts does. blockDim.x <= 1024; sm is the caller's, used once per launch.
 template <int NV>

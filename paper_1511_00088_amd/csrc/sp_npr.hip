@@ -21,11 +21,11 @@
 //    saves the 36 KB per hypercube written by k_npr_paths and read back by k_npr_contract).
 // Every kernel takes its hypercubes in XCD-aware order (block b on XCD b % 8 gets one of a contiguous range), so
 // that neighbouring hypercubes, which share cache lines of the fields and links, meet in one L2.
-// What bounds them: at 20^3x64 with 4 field sets the fused kernel keeps the vector units 63% and LDS 52% busy at three
-// waves per SIMD (160 registers: two matrices a thread). Half the products and LDS reads of the path build, eight sums
-// in 10 + 4 exchanges instead of 96, and one address per thread for the staged fields took it from 501 to 334 us (0.69 GB
-// of links, fields and results would take 111 us); on 12^3x24 with 9 sets the path links went from 26 to 23 us and a
-// contraction from 95 to 53 us.
+// What bounds them: LDS reads and FP64 products, both of them 60 to 70% of the time of the fused kernel at 20^3x64 with
+// 4 field sets. Half the products and LDS reads of the path build and one address per thread for the staged fields took
+// it from 503 to 319 us; one set at a time, its two sums added in one register without LDS, which fits 128 registers and
+// so four wavefronts per SIMD instead of three (two matrices a thread: 160), to 305 (0.69 GB of links, fields and results
+// would take 111 us). On 12^3x24 with 9 sets, path links and two contractions: 214, then 117, now 113 us.
 // The signs come from the anticommutation relations: gamma_X gamma_Y = (-1)^s(X,Y) gamma_{X xor Y} with
 // s(X,Y) = #{mu > nu : X_mu = Y_nu = 1}, gamma_X^dag = (-1)^{n(n-1)/2} gamma_X for n = |X|, tr gamma_0 = 4.
 #include "sp_launch.h"
@@ -232,71 +232,43 @@ __device__ __forceinline__ C bilinear(const double2 (&y)[3], const C (&U)[3][3],
     return b;
 }
 
-// Sums of eight values per thread over the 256 threads of a block; thread q < 8 returns that of value q. Each of the
-// first three exchanges of a wavefront halves the values a lane carries (the lane keeps the half that its bit names),
-// so that it takes 10 exchanges where eight separate sums take 48; then three lanes' worth of bits are summed as one
-// value. Ends with a barrier.
-__device__ __forceinline__ double block_fold8(const double (&v)[8]) {
-    __shared__ double sm[4][8];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    double a[4], b[2];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const double keep = lane & 4 ? v[4 + k] : v[k], give = lane & 4 ? v[k] : v[4 + k];
-        a[k] = keep + __shfl_xor(give, 4, 64);
-    }
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const double keep = lane & 2 ? a[2 + k] : a[k], give = lane & 2 ? a[k] : a[2 + k];
-        b[k] = keep + __shfl_xor(give, 2, 64);
-    }
-    double c = (lane & 1 ? b[1] : b[0]) + __shfl_xor(lane & 1 ? b[0] : b[1], 1, 64);
-    c += __shfl_xor(c, 8, 64);
-    c += __shfl_xor(c, 16, 64);
-    c += __shfl_xor(c, 32, 64);
-    if (lane < 8) sm[wid][lane] = c;
-    __syncthreads();
-    double t = 0.0;
-    if (threadIdx.x < 8) t = ((sm[0][lane] + sm[1][lane]) + sm[2][lane]) + sm[3][lane];
-    __syncthreads();
-    return t;
-}
-static_assert(NPR_CHUNK == 4, "block_fold8 sums the real and imaginary parts of four sets");
-
 // The contraction of hypercube z for every field set, by thread (A, C) of a block holding U_{A,D} and U_{C,B} in
 // registers; fs (LDS) stages the hypercube's field values of NPR_CHUNK field sets at a time. The caller has put the
 // first pass's values there, loaded early, so that their latency overlaps other work; those of later passes are
-// loaded as a pass starts (prefetching them across the arithmetic raises the kernel's registers past three waves per
-// SIMD).
+// loaded as a pass starts (prefetching them across the arithmetic raises the kernel's registers past four waves per
+// SIMD). One set at a time (a loop, not unrolled): that is what fits 128 registers, four wavefronts per SIMD.
 __device__ __forceinline__ void contract_sets(const NprArgs& a, int z, int base, const C (&uad)[3][3],
                                               const C (&ucb)[3][3], double2 (*fs)[4][16][3]) {
     const int A = threadIdx.x >> 4, Cc = threadIdx.x & 15;
     const int B = A ^ a.d1, D = Cc ^ a.d2;
+    __shared__ double sm[4][2 * NPR_CHUNK];
     const double sgn = (((a.neg1 >> A) ^ (a.neg2 >> Cc)) & 1) ? -1.0 : 1.0;
     for (int i0 = 0; i0 < a.n; i0 += NPR_CHUNK) {
         const int m = min(NPR_CHUNK, a.n - i0);
         if (i0 > 0) stage_put(a, i0, stage_get(a, base, i0), fs);
         __syncthreads();
-        double v[2 * NPR_CHUNK];
-#pragma unroll
-        for (int s = 0; s < NPR_CHUNK; ++s) {
-            v[2 * s] = v[2 * s + 1] = 0.0;
-            if (s >= m) continue;
+#pragma unroll 1
+        for (int s = 0; s < m; ++s) {
             // chib1(A)^T U_AD chi4(D) and chib3(C)^T U_CB chi2(B)
             const C b1 = bilinear(fs[s][0][A], uad, fs[s][3][D]), b2 = bilinear(fs[s][2][Cc], ucb, fs[s][1][B]);
             const C term = cmac({0.0, 0.0}, b1, b2);
-            v[2 * s] = sgn * term.re;
-            v[2 * s + 1] = sgn * term.im;
+            const double h = wave_sum2(sgn * term.re, sgn * term.im);
+            if ((threadIdx.x & 31) == 0) sm[threadIdx.x >> 6][2 * s + ((threadIdx.x >> 5) & 1)] = h;
         }
-        const double tot = block_fold8(v);  // ends with a barrier, so the staged values can be replaced next
-        if (threadIdx.x < 2 * m) ((double*)a.out)[((long)(i0 + (threadIdx.x >> 1)) * a.g.nz + z) * 2 + (threadIdx.x & 1)] = tot;
+        __syncthreads();
+        const int t = threadIdx.x;
+        if (t < 2 * m)
+            ((double*)a.out)[((long)(i0 + (t >> 1)) * a.g.nz + z) * 2 + (t & 1)] =
+                ((sm[0][t] + sm[1][t]) + sm[2][t]) + sm[3][t];
+        // of a next pass, stage_put comes after the barrier above, which ends the reads of fs; its barrier comes before
+        // sm is written again
     }
 }
 
 // From stored path links: the hypercube's contiguous 36 KB block comes in whole cache lines and goes through the path
 // area of LDS (a thread's own two matrices are scattered over it), which then becomes the field staging, as in
 // k_npr_fused.
-__global__ __launch_bounds__(256) void k_npr_contract(NprArgs a) {
+__global__ __launch_bounds__(256, 4) void k_npr_contract(NprArgs a) {
     const int z = remap_block(blockIdx.x, gridDim.x);
     const int A = threadIdx.x >> 4, Cc = threadIdx.x & 15;
     const int B = A ^ a.d1, D = Cc ^ a.d2;
@@ -322,7 +294,7 @@ __global__ __launch_bounds__(256) void k_npr_contract(NprArgs a) {
 // of path links per hypercube never travel to memory and back. The first pass's field values are loaded before
 // the paths are built; once every thread holds its two matrices the path area is reused for the field staging
 // (a barrier separates the two uses).
-__global__ __launch_bounds__(256) void k_npr_fused(NprArgs a, const double2* __restrict__ U) {
+__global__ __launch_bounds__(256, 4) void k_npr_fused(NprArgs a, const double2* __restrict__ U) {
     const int z = remap_block(blockIdx.x, gridDim.x);
     const int A = threadIdx.x >> 4, Cc = threadIdx.x & 15;
     const int B = A ^ a.d1, D = Cc ^ a.d2;
