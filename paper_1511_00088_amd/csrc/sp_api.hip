@@ -280,6 +280,7 @@ struct Layout {
     size_t total = 0;
     int inner = SP_F32, nbatch_rhs = 1;
     int total_blocks = 0;
+    bool many = false;  // one system per group, iterating as single systems (DescMany)
     LaunchCfg cfg;
 };
 
@@ -298,8 +299,26 @@ size_t sys_block_bytes(int Vh, int inner, size_t slot_off[NSLOT]) {
     return off;
 }
 
-// Groups systems and computes the workspace layout. n_rhs_max: 1 for a single solve, NB for batches.
-int make_layout(int nsys, const sp_system* systems, const sp_cg_params* prm, int n_rhs_max, Layout* L) {
+// Whether the systems of a batched solve iterate as single systems in common launches (DescMany) instead of in groups that
+// share their link loads: small lattices, whose five launches an iteration are bound by latency.
+bool many_systems(int nsys, const sp_system* systems, const sp_cg_params* prm) {
+    if (nsys < 2 || (prm->inner != SP_F32 && prm->inner != SP_F64)) return false;
+    const sp_system& a = systems[0];
+    Geom g, gi;
+    if (check_geom(a.g, &g)) return false;
+    if ((long)nsys * g.Vh > many_sites(prm->inner == SP_F64 ? SP_F64 : a.U->lo_prec, prm->inner)) return false;
+    for (int i = 0; i < nsys; ++i) {
+        const sp_system& s = systems[i];
+        if (check_geom(s.g, &gi) || memcmp(&g, &gi, sizeof g)) return false;
+        if (s.U->recon != a.U->recon || s.U->lo_prec != a.U->lo_prec) return false;
+    }
+    return true;
+}
+
+// Groups systems and computes the workspace layout. n_rhs_max: 1 for a single solve, NB for batches; many (with 1): the
+// layout of DescMany.
+int make_layout(int nsys, const sp_system* systems, const sp_cg_params* prm, int n_rhs_max, Layout* L, bool many = false) {
+    L->many = many;
     if (nsys <= 0 || !systems) return fail(SP_ERR_INVALID_ARG, "no systems");
     if (!prm) return fail(SP_ERR_INVALID_ARG, "params is null");
     if (!valid_prec(prm->inner)) return fail(SP_ERR_INVALID_ARG, "bad inner precision %d", prm->inner);
@@ -344,14 +363,15 @@ int make_layout(int nsys, const sp_system* systems, const sp_cg_params* prm, int
         // link-load policy stay the tuned ones. Measured: FP16 links with 128-thread blocks (the plain operator's
         // tuned shape) took the 20^3x64 solve from 21.9 to 25.8 ms.
         if (n_rhs_max == 1 && blocks_for(G.g.Vh, 256) <= FUSED_PARTIALS * 256) L->cfg.nt = 256;
-        L->cfg.quad = n_rhs_max == 1 && quad_lanes(G.g.Vh, lp, rc, prm->inner);
+        L->cfg.quad = n_rhs_max == 1 && quad_lanes(many ? nsys * G.g.Vh : G.g.Vh, lp, rc, prm->inner);
+        if (many) L->cfg.stream = 0;
     }
     // Groups of one gauge field stand in a row (bundles of up to BUNDLE) and share a first block: their blocks alternate.
     auto same_field = [](const GroupPlan& a, const GroupPlan& b) {
         return a.U->f64 == b.U->f64 && a.U->lo == b.U->lo && a.U->recon == b.U->recon && a.U->lo_prec == b.U->lo_prec &&
                !memcmp(&a.g, &b.g, sizeof a.g);
     };
-    for (size_t i = 0; i < L->groups.size(); ++i) {
+    for (size_t i = 0; i < L->groups.size() && !many; ++i) {
         size_t at = i + 1;
         for (size_t k = i + 1; k < L->groups.size(); ++k)
             if (same_field(L->groups[i], L->groups[k])) {
@@ -380,12 +400,23 @@ int make_layout(int nsys, const sp_system* systems, const sp_cg_params* prm, int
     L->states_off = off;
     off += align256(sizeof(SolverState) * 2 * nsys);
     L->gdesc_off = off;
-    off += align256(sizeof(GroupDev) * L->groups.size());
+    off += align256((many ? sizeof(DescSingle) : sizeof(GroupDev)) * L->groups.size());
     L->sdesc_off = off;
-    off += align256(sizeof(SysDev) * nsys);
+    if (!many) off += align256(sizeof(SysDev) * nsys);
     L->ctrl_bytes = off;
     // partials: sized for the smallest block size so that retuning never overflows them
     for (auto& G : L->groups) {
+        if (many) {
+            // sized for four lanes per site. The |r|^2 partials lie in the half of the first area that only a true residual
+            // (two values a block) uses: its system's next iteration applies the operator to p and reads none.
+            const size_t b = sizeof(double) * (size_t)G.nblk;
+            G.partials_off = off;
+            G.partials_r_off = off + b;
+            G.partials_p_off = off + 2 * b;
+            G.rec_off = off + 3 * b;
+            off += align256(sizeof(double) * (3 * (size_t)blocks_for(4 * G.g.Vh, 256) + 2));
+            continue;
+        }
         G.partials_off = off;
         off += align256(sizeof(double) * (size_t)(2 * NB) * blocks_for(G.g.Vh, 64));
         G.partials_p_off = off;
@@ -437,6 +468,7 @@ struct Plan {
 // DS_UPDATE_FUSED, k_xpay_fused).
 template <class D>
 bool fused_single(const Plan& pl) {
+    if (std::is_same<D, DescMany>::value) return true;  // many_systems admits small lattices only
     return std::is_same<D, DescSingle>::value && pl.nblocks <= FUSED_PARTIALS * pl.cfg.nt;
 }
 
@@ -460,32 +492,51 @@ hipError_t enqueue_iterations(const D& d, const Plan& pl, int count, hipStream_t
     return hipSuccess;
 }
 
-// The fused single-system iteration. Iteration i reads state buffer i % 2 (the descriptor's state and the
-// spare right after it) and writes the other; an odd count ends with a copy back, so that between chunks
-// the state is always in the descriptor's buffer.
-hipError_t enqueue_iterations_fused(const DescSingle& d0, const Plan& pl, int count, hipStream_t s) {
+// The descriptor with its two state buffers exchanged, the buffer a launch on the other descriptor writes to (of many
+// systems it is in the descriptor), and the copy from the second buffer back to the first.
+DescSingle other_buffer(DescSingle d) {
+    ++d.sys.st;
+    return d;
+}
+DescMany other_buffer(DescMany d) {
+    std::swap(d.st, d.next);
+    return d;
+}
+SolverState* out_buffer(const DescSingle& d) { return d.sys.st; }
+SolverState* out_buffer(const DescMany&) { return nullptr; }
+hipError_t copy_back(const DescSingle& from, const DescSingle& to, hipStream_t s) {
+    return launch_state_copy(from.sys.st, to.sys.st, s);
+}
+hipError_t copy_back(const DescMany& from, const DescMany& to, hipStream_t s) {
+    return launch_state_publish(from.st, to.st, to.n, s);
+}
+
+// The fused iteration of one system, or of many at once. Iteration i reads state buffer i % 2 (the descriptor's state
+// and its spare) and writes the other; an odd count ends with a copy back, so that between chunks the state is always in
+// the descriptor's buffer.
+template <class D>
+hipError_t enqueue_iterations_fused(const D& d0, const Plan& pl, int count, hipStream_t s) {
     const int use64 = pl.inner == SP_F64;
-    DescSingle d[2] = {d0, d0};
-    d[1].sys.st = d0.sys.st + 1;
+    const D d[2] = {d0, other_buffer(d0)};
     if (pl.inner == SP_F32 || pl.inner == SP_F64) {
         // two launches per iteration (t and p by recurrence in k_norm_rec); the chunk's last p update is
         // k_xpay_fused, so the next chunk starts from a p and t that the chunk boundary leaves consistent
         for (int i = 0; i < count; ++i) {
             hipError_t e;
-            if ((e = launch_norm_rec(d[i & 1], d[(i + 1) & 1].sys.st, pl.nblocks, pl.cfg, pl.lp, pl.recon, pl.inner,
+            if ((e = launch_norm_rec(d[i & 1], out_buffer(d[(i + 1) & 1]), pl.nblocks, pl.cfg, pl.lp, pl.recon, pl.inner,
                                      s)))
                 return e;
             if ((e = launch_dslash(d[(i + 1) & 1], pl.nblocks, pl.cfg, pl.lp, pl.recon, pl.inner, 0, S_T, S_R,
                                    DS_UPDATE_FUSED, G_ITER, use64, s)))
                 return e;
         }
-        hipError_t e = launch_xpay_fused(d[count & 1], d[(count + 1) & 1].sys.st, 1, pl.nblocks, pl.cfg, pl.inner, s);
+        hipError_t e = launch_xpay_fused(d[count & 1], out_buffer(d[(count + 1) & 1]), 1, pl.nblocks, pl.cfg, pl.inner, s);
         if (e) return e;
-        if ((count + 1) & 1) return launch_state_copy(d[1].sys.st, d[0].sys.st, s);
+        if ((count + 1) & 1) return copy_back(d[1], d[0], s);
         return hipSuccess;
     }
     for (int i = 0; i < count; ++i) {
-        const DescSingle& di = d[i & 1];
+        const D& di = d[i & 1];
         hipError_t e;
         if ((e = launch_dslash(di, pl.nblocks, pl.cfg, pl.lp, pl.recon, pl.inner, 1, S_P, S_T, DS_NORM, G_ITER,
                                use64, s)))
@@ -493,10 +544,10 @@ hipError_t enqueue_iterations_fused(const DescSingle& d0, const Plan& pl, int co
         if ((e = launch_dslash(di, pl.nblocks, pl.cfg, pl.lp, pl.recon, pl.inner, 0, S_T, S_R, DS_UPDATE_FUSED,
                                G_ITER, use64, s)))
             return e;
-        if ((e = launch_xpay_fused(di, d[(i + 1) & 1].sys.st, i + 1 == count, pl.nblocks, pl.cfg, pl.inner, s)))
+        if ((e = launch_xpay_fused(di, out_buffer(d[(i + 1) & 1]), i + 1 == count, pl.nblocks, pl.cfg, pl.inner, s)))
             return e;
     }
-    if (count & 1) return launch_state_copy(d[1].sys.st, d[0].sys.st, s);
+    if (count & 1) return copy_back(d[1], d[0], s);
     return hipSuccess;
 }
 
@@ -532,7 +583,7 @@ hipError_t enqueue_chunk(const D& d, const Plan& pl, int iters, hipStream_t s) {
     hipError_t e;
     // the fused iteration's chunk-end k_xpay_fused already folds x_lo into x64 when an update is due
     const bool fused = fused_single<D>(pl);
-    if constexpr (std::is_same<D, DescSingle>::value)
+    if constexpr (!std::is_same<D, DescBatch>::value)
         e = fused ? enqueue_iterations_fused(d, pl, iters, s) : enqueue_iterations(d, pl, iters, s);
     else
         e = enqueue_iterations(d, pl, iters, s);
@@ -663,6 +714,12 @@ int solve_impl(int nsys, const sp_system* systems, const sp_cg_params* prm, sp_c
     Layout L;
     int rc = make_layout(nsys, systems, prm, batched ? NB : 1, &L);
     if (rc) return rc;
+    if (batched && many_systems(nsys, systems, prm)) {
+        // a workspace that holds the groups but not this layout (at most a few KB more) keeps the groups
+        Layout M;
+        if ((rc = make_layout(nsys, systems, prm, 1, &M, true))) return rc;
+        if (ws_bytes >= M.total) L = M;
+    }
     char range[160];
     snprintf(range, sizeof range, "%s %dx%dx%dx%d inner=%d links=%d/r%d systems=%d", batched ? "sp_cg_solve_batched" : "sp_cg_solve",
              L.groups[0].g.X, L.groups[0].g.Y, L.groups[0].g.Z, L.groups[0].g.T, prm->inner,
@@ -718,14 +775,15 @@ int solve_impl(int nsys, const sp_system* systems, const sp_cg_params* prm, sp_c
         gd.blk0 = G.blk0;
         gd.nblk = G.nblk;
         gd.bundle = G.bundle;
-        hg[k] = gd;
+        if (!L.many) hg[k] = gd;
         for (int i : G.sys) {
             size_t so[NSLOT];
             sys_block_bytes(G.g.Vh, L.inner, so);
             SysDev sd;
             for (int sl = 0; sl < NSLOT; ++sl) sd.v[sl] = base + L.sys_off[i] + so[sl];
             sd.st = (SolverState*)(base + L.states_off) + i;
-            hs[sys_counter] = sd;
+            if (L.many) ((DescSingle*)hg)[k] = {gd, sd};
+            else hs[sys_counter] = sd;
             order[sys_counter] = i;
             ++sys_counter;
         }
@@ -757,21 +815,26 @@ int solve_impl(int nsys, const sp_system* systems, const sp_cg_params* prm, sp_c
 
     DescSingle ds;
     DescBatch db;
+    DescMany dm;
     memset(&ds, 0, sizeof ds);
+    memset(&dm, 0, sizeof dm);
     memset(&db, 0, sizeof db);
     if (!batched) {
         ds.grp = hg[0];
         ds.sys = hs[0];
+    } else if (L.many) {
+        dm.one = (const DescSingle*)(base + L.gdesc_off);
+        dm.st = (SolverState*)(base + L.states_off);
+        dm.next = dm.st + nsys;
+        dm.n = nsys;
     } else {
         db.grp = (const GroupDev*)(base + L.gdesc_off);
         db.sys = (const SysDev*)(base + L.sdesc_off);
         db.ngroups = (int)L.groups.size();
     }
     const bool zero_x0 = !prm->use_x0;
-    auto setup = [&]() {
-        return batched ? enqueue_setup(db, pl, zero_x0, stream) : enqueue_setup(ds, pl, zero_x0, stream);
-    };
-    HIP_TRY(setup());
+    auto with_desc = [&](auto f) { return !batched ? f(ds) : L.many ? f(dm) : f(db); };
+    HIP_TRY(with_desc([&](const auto& d) { return enqueue_setup(d, pl, zero_x0, stream); }));
 
     // with graphs, one per poll slot: each ends by copying the states into its slot. Near convergence the
     // chunks are shorter (tail iterations), so that the last one does not run many iterations past the point
@@ -781,8 +844,8 @@ int solve_impl(int nsys, const sp_system* systems, const sp_cg_params* prm, sp_c
     hipGraphExec_t exec[2] = {nullptr, nullptr}, exec_tail[2] = {nullptr, nullptr};
     auto graphs = [&](int len, hipGraphExec_t* out) -> hipError_t {
         for (int k = 0; k < 2; ++k) {
-            hipError_t e = batched ? chunk_graph(db, pl, len, dev_states, slots[k], nsys, &out[k])
-                                   : chunk_graph(ds, pl, len, dev_states, slots[k], nsys, &out[k]);
+            hipError_t e =
+                with_desc([&](const auto& d) { return chunk_graph(d, pl, len, dev_states, slots[k], nsys, &out[k]); });
             if (e) return e;
         }
         return hipSuccess;
@@ -825,7 +888,7 @@ int solve_impl(int nsys, const sp_system* systems, const sp_cg_params* prm, sp_c
             if (g) {
                 HIP_TRY(hipGraphLaunch(g, stream));
             } else {
-                HIP_TRY(batched ? enqueue_chunk(db, pl, len, stream) : enqueue_chunk(ds, pl, len, stream));
+                HIP_TRY(with_desc([&](const auto& d) { return enqueue_chunk(d, pl, len, stream); }));
                 HIP_TRY(hipMemcpyAsync(slots[c & 1], dev_states, sizeof(SolverState) * nsys, hipMemcpyDeviceToHost,
                                        stream));
             }
@@ -1265,6 +1328,9 @@ size_t sp_cg_workspace_bytes(int nsys, const sp_system* systems, const sp_cg_par
     std::lock_guard<std::mutex> lock(g_mu);
     Layout L;
     if (make_layout(nsys, systems, params, nsys > 1 ? NB : 1, &L)) return 0;
+    Layout M;
+    if (many_systems(nsys, systems, params) && !make_layout(nsys, systems, params, 1, &M, true))
+        L.total = std::max(L.total, M.total);
     return L.total;
 }
 

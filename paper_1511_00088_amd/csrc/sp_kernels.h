@@ -58,6 +58,14 @@ struct DescBatch {
     int ngroups;
 };
 
+// Several systems of one geometry that each iterate as a single system does (in-block decisions), their blocks alternating.
+// The states are double-buffered as a single system's: a launch reads st[i] and writes next[i].
+struct DescMany {
+    const DescSingle* one;  // [n]
+    SolverState *st, *next;
+    int n;
+};
+
 // --- descriptor access ---------------------------------------------------------------------------------
 // The group of a logical block, and the block's number in it.
 struct BlockOf {
@@ -79,10 +87,22 @@ __device__ __forceinline__ BlockOf block_of(const DescBatch& d, int lblk) {
     const int k = d.grp[last].bundle, rel = lblk - d.grp[last].blk0, blk = rel / k;
     return {last - (k - 1) + (rel - blk * k), blk};
 }
+__device__ __forceinline__ BlockOf block_of(const DescMany& d, int lblk) {
+    const int b = lblk / d.n;
+    return {lblk - b * d.n, b};
+}
 __device__ __forceinline__ const GroupDev& grp_of(const DescSingle& d, int) { return d.grp; }
+__device__ __forceinline__ const GroupDev& grp_of(const DescMany& d, int g) { return d.one[g].grp; }
 __device__ __forceinline__ const GroupDev& grp_of(const DescBatch& d, int g) { return d.grp[g]; }
 __device__ __forceinline__ const SysDev& sys_of(const DescSingle& d, int) { return d.sys; }
 __device__ __forceinline__ const SysDev& sys_of(const DescBatch& d, int i) { return d.sys[i]; }
+__device__ __forceinline__ const SysDev& sys_of(const DescMany& d, int i) { return d.one[i].sys; }
+__device__ __forceinline__ SolverState* state_of(const DescSingle& d, int) { return d.sys.st; }
+__device__ __forceinline__ SolverState* state_of(const DescBatch& d, int i) { return d.sys[i].st; }
+__device__ __forceinline__ SolverState* state_of(const DescMany& d, int i) { return d.st + i; }
+// Where a launch that takes the decisions writes the advanced state of system i (st_out: the single system's).
+__device__ __forceinline__ SolverState* next_state(const DescSingle&, SolverState* st_out, int) { return st_out; }
+__device__ __forceinline__ SolverState* next_state(const DescMany& d, SolverState*, int i) { return d.next + i; }
 
 // Block order: with remap, consecutive logical blocks (neighbouring lattice slabs) go to the same XCD.
 // The hardware hands block b to XCD b % 8; logical block = start of that XCD's contiguous range + b / 8.
@@ -119,14 +139,14 @@ template <int N, class D>
 __device__ __forceinline__ Rhs<N> rhs_of(const D& d, const GroupDev& G, int gate) {
     Rhs<N> h;
     if constexpr (N == 1) {
-        h.st[0] = sys_of(d, G.sys0).st;
+        h.st[0] = state_of(d, G.sys0);
         h.act[0] = G.nrhs > 0 && (gate == G_NONE || h.st[0] == nullptr || gate_flags_open(h.st[0]->flags, gate));
         h.any = h.act[0];
         return h;
     }
     h.any = false;
 #pragma unroll
-    for (int r = 0; r < N; ++r) h.st[r] = sys_of(d, G.sys0 + (r < G.nrhs ? r : 0)).st;
+    for (int r = 0; r < N; ++r) h.st[r] = state_of(d, G.sys0 + (r < G.nrhs ? r : 0));
     int f[N];
 #pragma unroll
     for (int r = 0; r < N; ++r) f[r] = (gate == G_NONE || h.st[r] == nullptr) ? 0 : h.st[r]->flags;
@@ -556,14 +576,16 @@ __global__ __launch_bounds__(256) void k_xpay(D d, int gate, int remap) {
 // (the descriptor's state) and block 0 writes the advanced state to st_out, which the next iteration's
 // launches read, so no block can see a half-written state. At a chunk end (chunk_end != 0) with a reliable
 // update due, the launch instead performs the update's first step, x64 += x_lo and x_lo = 0.
-template <int VP>
-__global__ __launch_bounds__(256) void k_xpay_fused(DescSingle d, SolverState* __restrict__ st_out, int chunk_end,
-                                                     int remap) {
+template <int VP, class D>
+__global__ __launch_bounds__(256) void k_xpay_fused(D d, SolverState* __restrict__ st_out, int chunk_end, int remap) {
     using R = typename Real<VP>::T;
     using VF = VecFmt<VP>;
-    const int gblk = logical_block(remap);
-    const GroupDev& G = d.grp;
-    const StateIn si = state_in(d.sys.st);
+    const BlockOf bo = block_of(d, logical_block(remap));
+    const int gblk = bo.blk;
+    const GroupDev& G = grp_of(d, bo.grp);
+    const SysDev& S = sys_of(d, bo.grp);
+    const SolverState* st = state_of(d, bo.grp);
+    const StateIn si = state_in(st);
     const double pq = G.rec[0];
     const int Vh = G.g.Vh;
     const int cb = gblk * blockDim.x + threadIdx.x;
@@ -575,21 +597,21 @@ __global__ __launch_bounds__(256) void k_xpay_fused(DescSingle d, SolverState* _
     strided_head<1>(part, head, src, G.nblk);
     Vec3<R> rv = vzero<R>(), pv = vzero<R>();
     if (live) {
-        rv = VF::load(d.sys.v[S_R], Vh, cb);
-        pv = VF::load(d.sys.v[S_P], Vh, cb);
+        rv = VF::load(S.v[S_R], Vh, cb);
+        pv = VF::load(S.v[S_P], Vh, cb);
     }
     __shared__ BlockSums<1> sm;
     strided_tail<1>(part, head, G.nblk);
     block_sum_all<1>(part, sm);
     const bool go = goes_on(si, pq, part[0], chunk_end != 0);
     if (gblk == 0 && threadIdx.x == 0) {
-        SolverState s = *d.sys.st;
+        SolverState s = *st;
         if (!(s.flags & (ST_DONE | ST_PENDING))) {
             fin_alpha(&s, pq);
             if (!(s.flags & ST_DONE)) fin_update(&s, part[0], chunk_end != 0);
             if (go) s.flags |= ST_T_STALE;  // p formed here: a following k_norm_rec applies D_oe to it
         }
-        *st_out = s;
+        *next_state(d, st_out, bo.grp) = s;
     }
     if constexpr (VP != F64) {
         // paused with nothing wrong: a reliable update is due
@@ -598,15 +620,15 @@ __global__ __launch_bounds__(256) void k_xpay_fused(DescSingle d, SolverState* _
         if (chunk_end != 0 && pending && !(si.flags & ST_DONE)) {
             // the reliable update that follows the chunk starts here: x64 += x_lo; x_lo = 0 (k_accum's step)
             if (live) {
-                Vec3<double> x = VecFmt<F64>::load(d.sys.v[S_X64], Vh, cb);
-                const Vec3<float> xl = VecFmt<F32>::load(d.sys.v[S_XLO], Vh, cb);
+                Vec3<double> x = VecFmt<F64>::load(S.v[S_X64], Vh, cb);
+                const Vec3<float> xl = VecFmt<F32>::load(S.v[S_XLO], Vh, cb);
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     x.c[i].re += (double)xl.c[i].re;
                     x.c[i].im += (double)xl.c[i].im;
                 }
-                VecFmt<F64>::store(d.sys.v[S_X64], Vh, cb, x);
-                VecFmt<F32>::store(d.sys.v[S_XLO], Vh, cb, vzero<float>());
+                VecFmt<F64>::store(S.v[S_X64], Vh, cb, x);
+                VecFmt<F32>::store(S.v[S_XLO], Vh, cb, vzero<float>());
             }
             return;
         }
@@ -620,7 +642,7 @@ __global__ __launch_bounds__(256) void k_xpay_fused(DescSingle d, SolverState* _
             pv.c[i].re = rv.c[i].re + beta * pv.c[i].re;
             pv.c[i].im = rv.c[i].im + beta * pv.c[i].im;
         }
-        const Vec3<R> ps = VF::store_rt(d.sys.v[S_P], Vh, cb, pv);
+        const Vec3<R> ps = VF::store_rt(S.v[S_P], Vh, cb, pv);
 #pragma unroll
         for (int i = 0; i < 3; ++i)
             dots[0] += (double)ps.c[i].re * (double)ps.c[i].re + (double)ps.c[i].im * (double)ps.c[i].im;
@@ -637,20 +659,22 @@ __global__ __launch_bounds__(256) void k_xpay_fused(DescSingle d, SolverState* _
 // state to st_out. When p was formed elsewhere (start, reliable update, end of the last chunk: ST_T_STALE)
 // the launch applies D_oe to p directly and takes no decision. Partials: Re<D_oe in, t> as DS_NORM, and
 // |p_i|^2 from the recurrence (the other paths leave the |p|^2 partials of the launch that formed p).
-template <int LP, int RECON, int VP, int POL = CACHED>
-__global__ __launch_bounds__(256) void k_norm_rec(DescSingle d, SolverState* __restrict__ st_out, int remap) {
+template <int LP, int RECON, int VP, int POL, class D>
+__global__ __launch_bounds__(256) void k_norm_rec(D d, SolverState* __restrict__ st_out, int remap) {
     using R = typename Real<VP>::T;
     using VF = VecFmt<VP>;
-    const int gblk = logical_block(remap);
-    const GroupDev& G = d.grp;
-    const SysDev& S = d.sys;
+    const BlockOf bo = block_of(d, logical_block(remap));
+    const int gblk = bo.blk;
+    const GroupDev& G = grp_of(d, bo.grp);
+    const SysDev& S = sys_of(d, bo.grp);
+    const SolverState* st = state_of(d, bo.grp);
     const Geom g = G.g;
     const int cb = site_index<POL>(gblk);
     const bool live = cb < g.Vh, lead = live && site_lead<POL>();
-    const StateIn si = state_in(S.st);
+    const StateIn si = state_in(st);
     const double pq = G.rec[0];
     if (si.flags & (ST_DONE | ST_PENDING)) {
-        if (gblk == 0 && threadIdx.x == 0) *st_out = *S.st;
+        if (gblk == 0 && threadIdx.x == 0) *next_state(d, st_out, bo.grp) = *st;
         return;
     }
     const bool direct = (si.flags & ST_T_STALE) != 0;
@@ -675,14 +699,14 @@ __global__ __launch_bounds__(256) void k_norm_rec(DescSingle d, SolverState* __r
         block_sum_all<1>(part, sm);
     }
     if (gblk == 0 && threadIdx.x == 0) {
-        SolverState s = *S.st;
+        SolverState s = *st;
         if (direct) {
             s.flags &= ~ST_T_STALE;
         } else {
             fin_alpha(&s, pq);
             if (!(s.flags & ST_DONE)) fin_update(&s, part[0], false);
         }
-        *st_out = s;
+        *next_state(d, st_out, bo.grp) = s;
     }
     if (!direct && !goes_on(si, pq, part[0], false)) return;  // paused or stopped: t, p and their partials stay
     const R beta = direct ? R(0) : (R)(part[0] / si.rho);

@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "sp_kernels.h"
 
 namespace sp {
@@ -37,6 +39,15 @@ static constexpr int NB = 4;
 // 224, 215 and 215.
 static constexpr size_t BUNDLE = 4;
 
+// Sites per parity, summed over the systems, up to which the systems of a batch iterate as single systems in common launches
+// (many_systems): two launches an iteration that take their own decisions, against five whose links a group loads once.
+// Small lattices are bound by the launches, large ones by the bytes. Measured per solve (tol 1e-10, m = 0.1, FP32 recon 12
+// unless said; groups against this, ms): 3 systems on 8^4 6.75 and 2.29, 32 on 8^4 7.98 and 3.74; 3 on 12^3x24 9.03 and
+// 3.74, 6 (recon 18) 9.8 and 4.5, 6 (FP64) 12.0 and 6.2; 3 on 16^3x32 (196,608 sites) 11.0 and 8.5, 4 (FP64) 15.7 and
+// 12.1, 6 (recon 18; 393,216) 13.7 and 11.8, 6 (FP16 links) 14.3 and 14.6, 16 (1,048,576) 21.4 and 24.3; 4 on 24^3x48
+// (recon 18; 1,327,104) 40.1 and 54.8; 8 on 20^3x64 (2,048,000) 47.9 and 54.8.
+inline long many_sites(int lp, int vp) { return lp == F32 && vp == F32 ? 400000 : 262144; }
+
 inline int blocks_for(int n, int nt) { return (n + nt - 1) / nt; }
 
 // The fused single-system iteration has every block sum all block partials of the previous launch (in the same
@@ -45,8 +56,18 @@ inline int blocks_for(int n, int nt) { return (n + nt - 1) / nt; }
 // latency overlaps the link loads; each block reads them all (8 bytes per block of the launch) from L2.
 static constexpr int FUSED_PARTIALS = 32;
 
-// Half operator (see k_dslash; mode DS_PLAIN, DS_NORM or DS_UPDATE). D = DescSingle (one system) or
-// DescBatch (up to NB per group).
+// Systems per group in the launches of a descriptor.
+template <class D>
+struct NOf {
+    static constexpr int value = 1;
+};
+template <>
+struct NOf<DescBatch> {
+    static constexpr int value = NB;
+};
+
+// Half operator (see k_dslash; mode DS_PLAIN, DS_NORM or DS_UPDATE). D = DescSingle (one system), DescBatch (up to NB
+// per group) or DescMany (FP32 and FP64 vectors, cached or quad gathers, modes DS_PLAIN in FP64 and DS_UPDATE_FUSED).
 template <class D>
 hipError_t launch_dslash(const D& d, int nblocks, LaunchCfg c, int lp, int recon, int vp, int p, int in_slot,
                          int out_slot, int mode, int gate, int use64, hipStream_t s);
@@ -58,13 +79,16 @@ template <class D>
 hipError_t launch_accum(const D& d, int nblocks, LaunchCfg c, hipStream_t s);
 template <class D>
 hipError_t launch_norm_b(const D& d, int nblocks, LaunchCfg c, hipStream_t s);
-// Fused p update of one system (k_xpay_fused): reads d's state, writes the advanced state to st_out.
-hipError_t launch_xpay_fused(const DescSingle& d, SolverState* st_out, int chunk_end, int nblocks, LaunchCfg c, int vp,
+// Fused p update of one system or of many (k_xpay_fused): reads d's state, writes the advanced state to st_out (of
+// several systems: to d.next).
+template <class D>
+hipError_t launch_xpay_fused(const D& d, SolverState* st_out, int chunk_end, int nblocks, LaunchCfg c, int vp,
                              hipStream_t s);
 hipError_t launch_state_copy(const SolverState* src, SolverState* dst, hipStream_t s);
 hipError_t launch_state_publish(const SolverState* src, SolverState* dst, int n, hipStream_t s);
-// First launch of the two-launch iteration of one system in FP32 or FP64 (k_norm_rec).
-hipError_t launch_norm_rec(const DescSingle& d, SolverState* st_out, int nblocks, LaunchCfg c, int lp, int recon, int vp,
+// First launch of the two-launch iteration of one system, or of many, in FP32 or FP64 (k_norm_rec).
+template <class D>
+hipError_t launch_norm_rec(const D& d, SolverState* st_out, int nblocks, LaunchCfg c, int lp, int recon, int vp,
                            hipStream_t s);
 // Second reduction stage (k_finalize), one block per group.
 template <class D>

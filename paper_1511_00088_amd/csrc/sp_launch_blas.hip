@@ -22,15 +22,6 @@ __global__ __launch_bounds__(256) void k_state_publish(const uint4* __restrict__
 static_assert(sizeof(SolverState) % sizeof(uint4) == 0, "states copy as 16-byte words");
 
 template <class D>
-struct NOf {
-    static constexpr int value = NB;
-};
-template <>
-struct NOf<DescSingle> {
-    static constexpr int value = 1;
-};
-
-template <class D>
 hipError_t launch_xpay(const D& d, int nblocks, LaunchCfg c, int vp, int gate, hipStream_t s) {
     constexpr int N = NOf<D>::value;
 #define SP_LAUNCH(VP)                                                                                      \
@@ -46,20 +37,25 @@ hipError_t launch_xpay(const D& d, int nblocks, LaunchCfg c, int vp, int gate, h
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_xpay_fused(const DescSingle& d, SolverState* st_out, int chunk_end, int nblocks, LaunchCfg c, int vp,
+template <class D>
+hipError_t launch_xpay_fused(const D& d, SolverState* st_out, int chunk_end, int nblocks, LaunchCfg c, int vp,
                              hipStream_t s) {
 #define SP_LAUNCH(VP)                                                                                      \
     do {                                                                                                   \
-        hipLaunchKernelGGL((k_xpay_fused<VP>), dim3(nblocks), dim3(c.nt), 0, s, d, st_out, chunk_end, c.remap); \
+        hipLaunchKernelGGL((k_xpay_fused<VP, D>), dim3(nblocks), dim3(c.nt), 0, s, d, st_out, chunk_end, c.remap); \
         return hipGetLastError();                                                                          \
     } while (0)
     if (vp == F64) SP_LAUNCH(F64);
     if (vp == F32) SP_LAUNCH(F32);
-    if (vp == F16) SP_LAUNCH(F16);
-    if (vp == BF16) SP_LAUNCH(BF16);
+    if constexpr (std::is_same<D, DescSingle>::value) {
+        if (vp == F16) SP_LAUNCH(F16);
+        if (vp == BF16) SP_LAUNCH(BF16);
+    }
 #undef SP_LAUNCH
     return hipErrorInvalidValue;
 }
+template hipError_t launch_xpay_fused<DescSingle>(const DescSingle&, SolverState*, int, int, LaunchCfg, int, hipStream_t);
+template hipError_t launch_xpay_fused<DescMany>(const DescMany&, SolverState*, int, int, LaunchCfg, int, hipStream_t);
 
 hipError_t launch_state_publish(const SolverState* src, SolverState* dst, int n, hipStream_t s) {
     const int words = (int)(n * sizeof(SolverState) / sizeof(uint4));
@@ -100,6 +96,7 @@ hipError_t launch_finalize(const D& d, int ngroups, int kind, int gate, hipStrea
     template hipError_t launch_norm_b<D>(const D&, int, LaunchCfg, hipStream_t);
 SP_INST(DescSingle)
 SP_INST(DescBatch)
+SP_INST(DescMany)
 #undef SP_INST
 
 hipError_t launch_pack_gauge(const Geom& g, const double* nat, int prec, int recon, void* out, void* f64, hipStream_t s) {

@@ -4,23 +4,19 @@
 namespace sp {
 
 template <class D>
-struct NOf {
-    static constexpr int value = NB;
-};
-template <>
-struct NOf<DescSingle> {
-    static constexpr int value = 1;
-};
-
-template <class D>
 hipError_t launch_dslash(const D& d, int nblocks, LaunchCfg c, int lp, int recon, int vp, int p, int in_slot,
                          int out_slot, int mode, int gate, int use64, hipStream_t s) {
     constexpr int N = NOf<D>::value;
+    constexpr bool MANY = std::is_same<D, DescMany>::value;
 // The streaming link loads are built for the single-system operator (N == 1) only; batched groups share each
 // link load among their right-hand sides and take the cached loads.
 #define SP_LAUNCH_NT(LP, RC, VP, POL)                                                                      \
     do {                                                                                                   \
-        if (mode == DS_PLAIN)                                                                              \
+        if constexpr (MANY && !(LP == F64)) {                                                              \
+            if (mode != DS_UPDATE_FUSED) return hipErrorInvalidValue;                                      \
+            hipLaunchKernelGGL((k_dslash<LP, RC, VP, N, D, DS_UPDATE_FUSED, POL>), dim3(nblocks), dim3(c.nt), 0, \
+                               s, d, p, in_slot, out_slot, gate, use64, c.remap);                         \
+        } else if (mode == DS_PLAIN)                                                                              \
             hipLaunchKernelGGL((k_dslash<LP, RC, VP, N, D, DS_PLAIN, POL>), dim3(nblocks), dim3(c.nt), 0, s, d, \
                                p, in_slot, out_slot, gate, use64, c.remap);                               \
         else if (mode == DS_NORM)                                                                          \
@@ -42,9 +38,12 @@ hipError_t launch_dslash(const D& d, int nblocks, LaunchCfg c, int lp, int recon
             if constexpr (VP == F32 || VP == F64) {                                                        \
                 if (c.quad) SP_LAUNCH_NT(LP, RC, VP, QUAD);                                                \
             }                                                                                              \
-            if (c.stream) SP_LAUNCH_NT(LP, RC, VP, STREAM);                                                \
+            if constexpr (!MANY) {                                                                         \
+                if (c.stream) SP_LAUNCH_NT(LP, RC, VP, STREAM);                                            \
+            }                                                                                              \
         }                                                                                                  \
-        SP_LAUNCH_NT(LP, RC, VP, CACHED);                                                                   \
+        if constexpr (!MANY || VP == F32 || VP == F64) SP_LAUNCH_NT(LP, RC, VP, CACHED); \
+        return hipErrorInvalidValue;                                                                  \
     } while (0)
     if (lp == F64 && recon == 18 && vp == F64) SP_LAUNCH(F64, 18, F64);
     if (lp == F32 && recon == 18 && vp == F32) SP_LAUNCH(F32, 18, F32);
@@ -66,19 +65,24 @@ hipError_t launch_dslash(const D& d, int nblocks, LaunchCfg c, int lp, int recon
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_norm_rec(const DescSingle& d, SolverState* st_out, int nblocks, LaunchCfg c, int lp, int recon, int vp,
+template <class D>
+hipError_t launch_norm_rec(const D& d, SolverState* st_out, int nblocks, LaunchCfg c, int lp, int recon, int vp,
                            hipStream_t s) {
 #define SP_LAUNCH(LP, RC, VP)                                                                              \
     do {                                                                                                   \
-        if (c.quad)                                                                                        \
-            hipLaunchKernelGGL((k_norm_rec<LP, RC, VP, QUAD>), dim3(nblocks), dim3(c.nt), 0, s, d, st_out,  \
+        if (c.quad) {                                                                                      \
+            hipLaunchKernelGGL((k_norm_rec<LP, RC, VP, QUAD, D>), dim3(nblocks), dim3(c.nt), 0, s, d, st_out, \
                                c.remap);                                                                   \
-        else if (c.stream)                                                                                 \
-            hipLaunchKernelGGL((k_norm_rec<LP, RC, VP, STREAM>), dim3(nblocks), dim3(c.nt), 0, s, d, st_out,  \
-                               c.remap);                                                                   \
-        else                                                                                               \
-            hipLaunchKernelGGL((k_norm_rec<LP, RC, VP, CACHED>), dim3(nblocks), dim3(c.nt), 0, s, d, st_out, \
-                               c.remap);                                                                   \
+            return hipGetLastError();                                                                      \
+        }                                                                                                  \
+        if constexpr (std::is_same<D, DescSingle>::value) {                                                \
+            if (c.stream) {                                                                                \
+                hipLaunchKernelGGL((k_norm_rec<LP, RC, VP, STREAM, D>), dim3(nblocks), dim3(c.nt), 0, s, d, st_out, \
+                                   c.remap);                                                               \
+                return hipGetLastError();                                                                  \
+            }                                                                                              \
+        }                                                                                                  \
+        hipLaunchKernelGGL((k_norm_rec<LP, RC, VP, CACHED, D>), dim3(nblocks), dim3(c.nt), 0, s, d, st_out, c.remap); \
         return hipGetLastError();                                                                          \
     } while (0)
     if (lp == F64 && recon == 18 && vp == F64) SP_LAUNCH(F64, 18, F64);
@@ -94,6 +98,8 @@ hipError_t launch_norm_rec(const DescSingle& d, SolverState* st_out, int nblocks
 #undef SP_LAUNCH
     return hipErrorInvalidValue;
 }
+template hipError_t launch_norm_rec<DescSingle>(const DescSingle&, SolverState*, int, LaunchCfg, int, int, int, hipStream_t);
+template hipError_t launch_norm_rec<DescMany>(const DescMany&, SolverState*, int, LaunchCfg, int, int, int, hipStream_t);
 
 template <class D>
 hipError_t launch_resid(const D& d, int nblocks, LaunchCfg c, int op, int init, hipStream_t s) {
@@ -123,5 +129,8 @@ template hipError_t launch_dslash<DescBatch>(const DescBatch&, int, LaunchCfg, i
                                              int, int, hipStream_t);
 template hipError_t launch_resid<DescSingle>(const DescSingle&, int, LaunchCfg, int, int, hipStream_t);
 template hipError_t launch_resid<DescBatch>(const DescBatch&, int, LaunchCfg, int, int, hipStream_t);
+template hipError_t launch_dslash<DescMany>(const DescMany&, int, LaunchCfg, int, int, int, int, int, int, int, int, int,
+                                            hipStream_t);
+template hipError_t launch_resid<DescMany>(const DescMany&, int, LaunchCfg, int, int, hipStream_t);
 
 }  // namespace sp

@@ -308,7 +308,8 @@ def _true_resid_oracle(dims, U, m, b, x):
 def test_alternating_groups_of_a_field_change_nothing(na, nb):
     """Systems of two fields listed in turn: field A's make up to six groups (bundles of four and the rest, the last group
     not full), field B's lattice is smaller. Every solution equals, bit for bit, the one of a batch of its own field alone
-    (the launch shape is that of the larger lattice in both; field B is compared at that shape through the oracle)."""
+    but for one system of another extent, which keeps it in groups (the launch shape is that of the larger lattice in both;
+    field B is compared at that shape through the oracle)."""
     announce(f"bundles of {na} and {nb} systems")
     da, db = (6, 4, 8, 10), (4, 4, 4, 6)
     UA, UB = li.near_identity_links(da, 0.3, 471), li.near_identity_links(db, 0.3, 472)
@@ -322,7 +323,8 @@ def test_alternating_groups_of_a_field_change_nothing(na, nb):
                 both.append((G, 0.05 + 0.01 * k, bs[k]))
                 where.append((f, k))
     xs, st = sp.cg_solve_batched(both, tol=1e-9, workspace=sp.Workspace())
-    xa, _ = sp.cg_solve_batched([(GA, 0.05 + 0.01 * k, b) for k, b in enumerate(ba)], tol=1e-9, workspace=sp.Workspace())
+    xa, _ = sp.cg_solve_batched([(GA, 0.05 + 0.01 * k, b) for k, b in enumerate(ba)] + both[1:2], tol=1e-9,
+                                workspace=sp.Workspace())
     assert all(s.converged for s in st)
     for x, (f, k) in zip(xs, where):
         if f == 0:
@@ -330,3 +332,28 @@ def test_alternating_groups_of_a_field_change_nothing(na, nb):
         else:
             ref = oracle.cg_solve(db, UB, 0.05 + 0.01 * k, to_host(bb[k]), tol=1e-12)[0]
             assert rel_err_2(to_host(x), ref) <= 1e-6
+
+
+@pytest.mark.parametrize("dims,n,inner,recon,lo", [
+    ((4, 4, 4, 4), 2, "f32", 12, "f32"),       # two blocks a system
+    ((6, 4, 2, 10), 5, "f64", 18, "f64"),      # 240 sites a parity: a last block not full
+    ((6, 8, 10, 6), 3, "f32", 8, "f32"),
+    ((4, 6, 4, 8), 70, "f32", 18, "i16"),      # more systems than a wavefront has lanes
+    ((12, 12, 12, 12), 2, "f32", 18, "f32"),   # a lane per site
+])
+def test_small_batches_iterate_as_single_systems(dims, n, inner, recon, lo):
+    """Small lattices of one extent share their launches but not their sums: every system of the batch takes the steps it
+    takes alone, so solution, iterations and reliable updates are the same bit for bit, whatever the others do (two fields,
+    masses a decade apart, a zero source among them), and repeated."""
+    announce(f"batch of single systems: {dims} x {n} {inner} r{recon} links {lo}")
+    U = [li.near_identity_links(dims, 0.3, 481 + k) for k in range(2)]
+    G = [gauge(dims, u, lo, recon) for u in U]
+    src = [li.gaussian_even_source(dims, 4900 + k) * (0.0 if k == n - 1 and n > 2 else 1.0) for k in range(n)]
+    systems = [(G[k % 2], 0.05 * 10.0 ** (k / n), to_dev(b)) for k, b in enumerate(src)]
+    ws = sp.Workspace()
+    xs, st = sp.cg_solve_batched(systems, tol=1e-10, inner=inner, workspace=ws)
+    again, _ = sp.cg_solve_batched(systems, tol=1e-10, inner=inner, workspace=ws)
+    for k, (g, m, b) in enumerate(systems):
+        alone, st1 = sp.cg_solve(g, m, b, tol=1e-10, inner=inner)
+        assert st[k].converged and (st[k].iters, st[k].reliable_updates) == (st1.iters, st1.reliable_updates), k
+        assert torch.equal(xs[k], alone) and torch.equal(xs[k], again[k]), k
