@@ -90,7 +90,7 @@ hipError_t launch_state_publish(const SolverState* src, SolverState* dst, int n,
 template <class D>
 hipError_t launch_norm_rec(const D& d, SolverState* st_out, int nblocks, LaunchCfg c, int lp, int recon, int vp,
                            hipStream_t s);
-// Second reduction stage (k_finalize), one block per group.
+// Second reduction stage (k_finalize), one block per system.
 template <class D>
 hipError_t launch_finalize(const D& d, int ngroups, int kind, int gate, hipStream_t s);
 

@@ -85,7 +85,7 @@ hipError_t launch_norm_b(const D& d, int nblocks, LaunchCfg c, hipStream_t s) {
 template <class D>
 hipError_t launch_finalize(const D& d, int ngroups, int kind, int gate, hipStream_t s) {
     constexpr int N = NOf<D>::value;
-    hipLaunchKernelGGL((k_finalize<N, D>), dim3(ngroups), dim3(1024), 0, s, d, kind, gate);
+    hipLaunchKernelGGL((k_finalize<N, D>), dim3(ngroups * N), dim3(1024), 0, s, d, kind, gate);
     return hipGetLastError();
 }
 
