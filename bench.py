@@ -189,13 +189,14 @@ def pin_launch(sp, key, cfg):
         os.unlink(path)
 
 
-def tuned_entry(path, key):
-    """The tuned launch of key in a table file, or the library's default."""
+def tuned_entry(path, key, default=None):
+    """The tuned launch of key in a table file, or the default (256 threads, XCD-aware order, cached loads)."""
+    base = {"nt": 256, "remap": 1, "stream": 0}
     try:
         with open(path) as f:
-            return {"nt": 256, "remap": 1, "stream": 0, **json.load(f)[key]}
+            return {**base, **json.load(f)[key]}
     except (OSError, KeyError, ValueError):
-        return {"nt": 256, "remap": 1, "stream": 0}
+        return default or base
 
 
 def stream_ceiling(sp, torch, dev, stream, flush, log, nbytes=2 << 30, small_bytes=None):
@@ -756,6 +757,8 @@ def main():
     # that flushes the Infinity Cache, net of the flush: every byte from HBM, the roofline figure)
     key = tune_key(dims, lprec, args.recon, args.inner)
     tuned = tuned_entry(args.tune_file, key)
+    # the solver's own link loads: its "/solve" entry, where there is one
+    solver_stream = tuned_entry(args.tune_file, key + "/solve", tuned).get("stream", 0)
     policies = {}
     for pol, name in ((0, "cached"), (1, "streaming")):
         pin_launch(sp, key, dict(tuned, stream=pol))
@@ -763,9 +766,9 @@ def main():
         tf = time_flushed(torch, lambda: sp.dslash_packed(G, args.inner, inp, 1, out), flush, stream)
         policies[name] = {"warm_us": tw * 1e6, "flushed_us": tf * 1e6, "warm_hbm_frac": alg_bytes / tw / 1e9 / HBM_PEAK_GBS,
                           "flushed_hbm_frac": alg_bytes / tf / 1e9 / HBM_PEAK_GBS,
-                          "solver_uses": pol == tuned.get("stream", 0)}
+                          "solver_uses": pol == solver_stream}
     pin_launch(sp, key, tuned)
-    solver_pol = "streaming" if tuned.get("stream", 0) else "cached"
+    solver_pol = "streaming" if solver_stream else "cached"
     best_pol = min(policies, key=lambda k: policies[k]["flushed_us"])
     t_d = policies[solver_pol]["warm_us"] / 1e6
     t_df = policies[best_pol]["flushed_us"] / 1e6

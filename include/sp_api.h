@@ -199,7 +199,8 @@ int sp_cg_solve(const sp_geom* g, const sp_gauge* U, double mass, const double* 
  * field share each link load, and independent systems are the unit that spreads over GPUs without communication.
  * Solve nsys independent systems together: systems sharing a gauge field and geometry form groups of up
  * to 4 right-hand sides; all groups advance in one launch per kernel, captured in a hipGraph per chunk
- * of iterations; converged systems stop updating while the others continue. Groups may differ in volume
+ * of iterations (FP32 and FP64 systems of one small geometry, up to some 400,000 sites per parity in all, advance
+ * in common launches without forming groups, with the launch shape of single solves); converged systems stop updating while the others continue. Groups may differ in volume
  * and time boundary; a zero b_e stops at the first residual check with x_e = 0. stats: host array of nsys
  * (nullable). Returns SP_OK if every system converged, SP_NOT_CONVERGED if any did not, or an error. When
  * some systems break down (SP_ERR_BREAKDOWN), stats[i].status names them and the other systems' x_e and

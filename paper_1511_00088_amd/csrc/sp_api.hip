@@ -16,8 +16,8 @@
 //   update and t = D_oe r + beta t (the recurrence of t = D_oe p) in one, alpha and the x and r updates in
 //   the other, each block forming the scalars from the block partials of the launch before; the chunk
 //   ends with a p update alone, after which t is formed from p directly. With 16-bit storage a single
-//   system takes three (t = D_oe p, the update, the p update), and batched groups take five: two one-block
-//   finalize launches between them.
+//   system takes three (t = D_oe p, the update, the p update), and batched groups take five: two finalize
+//   launches between them. Batches of small lattices take the two launches of a single system (many_systems).
 // Plain FP64 CG is the same schedule with FP64 vectors, x updated in place and the FP64 true residual
 // computed only at apparent convergence.
 #include <hip/hip_runtime.h>

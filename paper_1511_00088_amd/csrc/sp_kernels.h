@@ -237,7 +237,7 @@ __device__ __forceinline__ void block_partials(double* dst, int gblk, double (&v
 //   DS_NORM  : t = D_oe p (out), block partials of Re<t, t_stored>; with |p|^2 from the last p update this
 //              gives Re<p, A p> = m^2 |p|^2 + |D_oe p|^2 and alpha, since D_eo = -D_oe^dag for any links
 //   DS_UPDATE: q = m^2 p - D_eo t (not stored); x += alpha p; r -= alpha q; block partials of |r|^2
-//   DS_UPDATE_FUSED (one system): as DS_UPDATE, but every block forms alpha itself from the partials of
+//   DS_UPDATE_FUSED (one system, or each of DescMany): as DS_UPDATE, but every block forms alpha itself from the partials of
 //              |D_oe p|^2 and |p|^2 (summed in the same order in every block, so all blocks agree bit for
 //              bit); the first partials are loaded before the gathers and summed after them. Saves the
 //              alpha finalize launch when the partials are few; |r|^2 partials go to partials_r, Re<p,Ap>
@@ -570,10 +570,10 @@ __global__ __launch_bounds__(256) void k_xpay(D d, int gate, int remap) {
     block_partials<N>(G.partials_p, gblk, dots);
 }
 
-// One system, after DS_UPDATE_FUSED: every block sums the |r|^2 partials (same order in every block) and
+// One system (of D = DescMany: each), after DS_UPDATE_FUSED: every block of it sums the |r|^2 partials (same order in every block) and
 // takes the decisions of the update finalize itself (breakdown, convergence and reliable-update triggers,
-// beta), then p = r + beta p with |p|^2 partials. The state is double-buffered: all blocks read st_in
-// (the descriptor's state) and block 0 writes the advanced state to st_out, which the next iteration's
+// beta), then p = r + beta p with |p|^2 partials. The state is double-buffered: all blocks read the
+// descriptor's state and block 0 writes the advanced state to next_state, which the next iteration's
 // launches read, so no block can see a half-written state. At a chunk end (chunk_end != 0) with a reliable
 // update due, the launch instead performs the update's first step, x64 += x_lo and x_lo = 0.
 template <int VP, class D>
@@ -650,13 +650,14 @@ __global__ __launch_bounds__(256) void k_xpay_fused(D d, SolverState* __restrict
     block_partials<1>(G.partials_p, gblk, dots);
 }
 
-// The first launch of an iteration of one system in FP32 or FP64 (with DS_UPDATE_FUSED the second). It
+// The first launch of an iteration of one system, or of each of D = DescMany, in FP32 or FP64 (with DS_UPDATE_FUSED
+// the second). It
 // replaces the p update and t = D_oe p of the three-launch iteration by the recurrence
 //   p_i = r_i + beta p_{i-1},   t_i = D_oe p_i = D_oe r_i + beta t_{i-1},
 // so that the operator is applied to r_i, which is complete when the launch starts, while p_i is formed in
 // the same launch (each thread also updates the even site with its own index). Every block first takes the
 // decisions of the last update from its |r|^2 partials (as k_xpay_fused does); block 0 writes the advanced
-// state to st_out. When p was formed elsewhere (start, reliable update, end of the last chunk: ST_T_STALE)
+// state to next_state. When p was formed elsewhere (start, reliable update, end of the last chunk: ST_T_STALE)
 // the launch applies D_oe to p directly and takes no decision. Partials: Re<D_oe in, t> as DS_NORM, and
 // |p_i|^2 from the recurrence (the other paths leave the |p|^2 partials of the launch that formed p).
 template <int LP, int RECON, int VP, int POL, class D>

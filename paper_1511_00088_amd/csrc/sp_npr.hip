@@ -21,11 +21,11 @@
 //    saves the 36 KB per hypercube written by k_npr_paths and read back by k_npr_contract).
 // Every kernel takes its hypercubes in XCD-aware order (block b on XCD b % 8 gets one of a contiguous range), so
 // that neighbouring hypercubes, which share cache lines of the fields and links, meet in one L2.
-// What bounds them: LDS reads and FP64 products, both of them 60 to 70% of the time of the fused kernel at 20^3x64 with
-// 4 field sets. Half the products and LDS reads of the path build and one address per thread for the staged fields took
-// it from 503 to 319 us; one set at a time, its two sums added in one register without LDS, which fits 128 registers and
-// so four wavefronts per SIMD instead of three (two matrices a thread: 160), to 305 (0.69 GB of links, fields and results
-// would take 111 us). On 12^3x24 with 9 sets, path links and two contractions: 214, then 117, now 113 us.
+// What bounds them: instruction issue and LDS. At 20^3x64 with 4 field sets the fused kernel keeps the vector units 76%
+// and LDS 61% busy (a quarter of that bank conflicts). Half the products and LDS reads of the path build and one address
+// per thread for the staged fields took it from 503 to 319 us; one set at a time, its two sums added in one register
+// without LDS, which fits 128 registers and so four wavefronts per SIMD instead of three (two matrices a thread: 160), to
+// 305 (0.69 GB of links, fields and results would take 111 us). On 12^3x24 with 9 sets, path links and two contractions: 214, then 117, now 113 us.
 // The signs come from the anticommutation relations: gamma_X gamma_Y = (-1)^s(X,Y) gamma_{X xor Y} with
 // s(X,Y) = #{mu > nu : X_mu = Y_nu = 1}, gamma_X^dag = (-1)^{n(n-1)/2} gamma_X for n = |X|, tr gamma_0 = 4.
 #include "sp_launch.h"
