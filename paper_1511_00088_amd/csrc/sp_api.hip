@@ -358,12 +358,12 @@ int make_layout(int nsys, const sp_system* systems, const sp_cg_params* prm, int
         const int lp = prm->inner == SP_F64 ? SP_F64 : G.U->lo_prec;
         const int rc = prm->inner == SP_F64 ? 18 : G.U->recon;
         L->cfg = n_rhs_max > 1 ? tuned_cfg_batched(G.g, lp, rc, prm->inner) : tuned_cfg_solve(G.g, lp, rc, prm->inner);
-        // one system: 256-thread blocks whenever they admit the fused iteration, whose launches have every block
-        // sum the partials of all blocks (smaller blocks mean more partials per block); the block order and the
-        // link-load policy stay the tuned ones. Measured: FP16 links with 128-thread blocks (the plain operator's
-        // tuned shape) took the 20^3x64 solve from 21.9 to 25.8 ms.
-        if (n_rhs_max == 1 && blocks_for(G.g.Vh, 256) <= FUSED_PARTIALS * 256) L->cfg.nt = 256;
-        L->cfg.quad = n_rhs_max == 1 && quad_lanes(many ? nsys * G.g.Vh : G.g.Vh, lp, rc, prm->inner);
+        // one system: the fused iteration's block size (solve_threads) whenever 256 threads admit that iteration; the
+        // block order and the link-load policy stay the tuned ones
+        const int sites = many ? nsys * G.g.Vh : G.g.Vh;
+        L->cfg.quad = n_rhs_max == 1 && quad_lanes(sites, lp, rc, prm->inner);
+        if (n_rhs_max == 1 && blocks_for(G.g.Vh, 256) <= FUSED_PARTIALS * 256)
+            L->cfg.nt = solve_threads(L->cfg.quad ? 4 * G.g.Vh : G.g.Vh);
         if (many) L->cfg.stream = 0;
     }
     // Groups of one gauge field stand in a row (bundles of up to BUNDLE) and share a first block: their blocks alternate.
@@ -404,24 +404,24 @@ int make_layout(int nsys, const sp_system* systems, const sp_cg_params* prm, int
     L->sdesc_off = off;
     if (!many) off += align256(sizeof(SysDev) * nsys);
     L->ctrl_bytes = off;
-    // partials: sized for the smallest block size so that retuning never overflows them
+    // partials: sized for the smallest block size so that retuning never overflows them. A system that takes its own
+    // decisions has its |r|^2 partials in the half of the first area that only a true residual (two values a block)
+    // uses, after which the system's next iteration reads none: four lanes per site mean up to 4 Vh / 64 blocks.
     for (auto& G : L->groups) {
         if (many) {
-            // sized for four lanes per site. The |r|^2 partials lie in the half of the first area that only a true residual
-            // (two values a block) uses: its system's next iteration applies the operator to p and reads none.
             const size_t b = sizeof(double) * (size_t)G.nblk;
             G.partials_off = off;
             G.partials_r_off = off + b;
             G.partials_p_off = off + 2 * b;
             G.rec_off = off + 3 * b;
-            off += align256(sizeof(double) * (3 * (size_t)blocks_for(4 * G.g.Vh, 256) + 2));
+            off += align256(3 * b + sizeof(double) * 2);
             continue;
         }
         G.partials_off = off;
         off += align256(sizeof(double) * (size_t)(2 * NB) * blocks_for(G.g.Vh, 64));
         G.partials_p_off = off;
         off += align256(sizeof(double) * (size_t)NB * blocks_for(G.g.Vh, 64));
-        G.partials_r_off = off;
+        G.partials_r_off = n_rhs_max == 1 ? G.partials_off + sizeof(double) * (size_t)G.nblk : off;
         off += align256(sizeof(double) * (size_t)blocks_for(G.g.Vh, 64));
         G.rec_off = off;
         off += align256(sizeof(double) * 2);

@@ -42,8 +42,8 @@ static constexpr size_t BUNDLE = 4;
 // Sites per parity, summed over the systems, up to which the systems of a batch iterate as single systems in common launches
 // (many_systems): two launches an iteration that take their own decisions, against five whose links a group loads once.
 // Small lattices are bound by the launches, large ones by the bytes. Measured per solve (tol 1e-10, m = 0.1, FP32 recon 12
-// unless said; groups against this, ms): 3 systems on 8^4 6.75 and 2.29, 32 on 8^4 7.98 and 3.74; 3 on 12^3x24 9.03 and
-// 3.74, 6 (recon 18) 9.8 and 4.5, 6 (FP64) 12.0 and 6.2; 3 on 16^3x32 (196,608 sites) 11.0 and 8.5, 4 (FP64) 15.7 and
+// unless said; groups against this, ms): 3 systems on 8^4 6.75 and 2.02, 32 on 8^4 7.98 and 3.69; 3 on 12^3x24 9.03 and
+// 3.58, 6 (recon 18) 9.8 and 4.5, 6 (FP64, 256 threads) 12.0 and 6.2; 3 on 16^3x32 (196,608 sites) 11.0 and 8.5, 4 (FP64) 15.7 and
 // 12.1, 6 (recon 18; 393,216) 13.7 and 11.8, 6 (FP16 links) 14.3 and 14.6, 16 (1,048,576) 21.4 and 24.3; 4 on 24^3x48
 // (recon 18; 1,327,104) 40.1 and 54.8; 8 on 20^3x64 (2,048,000) 47.9 and 54.8.
 inline long many_sites(int lp, int vp) { return lp == F32 && vp == F32 ? 400000 : 262144; }
@@ -65,6 +65,17 @@ template <>
 struct NOf<DescBatch> {
     static constexpr int value = NB;
 };
+
+// Threads per block of the fused iteration, for `lanes` lanes of a system (a site has one or four): the fewest that keep
+// it to one block a CU. Small lattices then spread over the chip, and a block reduces fewer wavefronts; with more
+// blocks than CUs each of them sums more partials for nothing. Measured per solve (ms; 64, 128 and 256 threads): 8^4 FP32
+// recon 12 with four lanes (8,192 in all) 2.28, 2.49 and 2.68, FP64 2.31, 2.63 and 3.18, BF16 with one lane 4.67, 4.87 and
+// 5.09; 16,384 lanes 2.68, 2.88 and 3.16; 20,736 (12^3x24, recon 18) 3.71, 3.52 and 3.97, FP64 4.57, 4.44 and 5.21, BF16
+// 6.25, 5.94 and 6.18; 32,000 2.96, 2.69 and 2.92; 38,416 4.81, 4.40 and 4.41; 65,536 (16^3x32, recon 12) 6.20, 5.58 and
+// 5.07; 82,944 (12^3x24, recon 12, four lanes) 4.51, 3.83 and 3.79; the 20^3x64 solve on FP16 links 25.8 with 128 and 21.9
+// with 256. Of several systems in common launches each block sums its own system's partials, so the lanes of one count: 3
+// systems on 8^4 2.01 against 2.25 with 256, 4 on 10^3x20 3.49 against 3.67, 4 in FP64 on 12^3x24 5.14 against 5.92.
+inline int solve_threads(int lanes) { return lanes <= 64 * 256 ? 64 : lanes <= 128 * 256 ? 128 : 256; }
 
 // Half operator (see k_dslash; mode DS_PLAIN, DS_NORM or DS_UPDATE). D = DescSingle (one system), DescBatch (up to NB
 // per group) or DescMany (FP32 and FP64 vectors, cached or quad gathers, modes DS_PLAIN in FP64 and DS_UPDATE_FUSED).

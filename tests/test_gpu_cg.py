@@ -468,3 +468,27 @@ def test_fast_converging_systems(inner):
             err = rel_err_2(to_host(x), xr)
             announce(f"  iters={st.iters} ru={st.reliable_updates} err={err:.2e}")
             assert st.converged and st.iters <= cap and err <= 1e-6
+
+
+@pytest.mark.parametrize("dims,inner,recon", [
+    ((8, 8, 8, 16), "f32", 12),     # four lanes a site, 16,384: 256 blocks of 64 threads
+    ((6, 8, 10, 18), "f32", 12),    # 17,280: 128 threads, the last block not full
+    ((10, 10, 10, 18), "f32", 12),  # 36,000: 256 threads
+    ((12, 12, 12, 12), "f64", 18),  # a lane a site, 10,368: 64 threads
+    ((10, 10, 18, 20), "f32", 18),  # 18,000: 128 threads
+    ((12, 16, 16, 24), "f64", 18),  # 36,864: 256 threads
+    ((2, 4, 2, 6), "bf16", 12),     # less than one wavefront
+])
+def test_block_sizes_of_the_fused_iteration(dims, inner, recon):
+    """Either side of each block size: the solution within 1e-6 of the oracle's 1e-12 solve (residual 1e-8, as everywhere
+    here), its true residual the oracle's, and a second solve bit for bit the first."""
+    U = li.near_identity_links(dims, 0.3, 231)
+    b = li.gaussian_even_source(dims, 232)
+    G = gauge(dims, U, inner, recon)
+    announce(f"cg block size {dims} {inner} r{recon}")
+    x, st = sp.cg_solve(G, 0.1, to_dev(b), tol=1e-8, inner=inner)
+    again, _ = sp.cg_solve(G, 0.1, to_dev(b), tol=1e-8, inner=inner)
+    xr, _, _, _ = oracle.cg_solve(dims, U, 0.1, b, tol=1e-12)
+    assert st.converged and torch.equal(x, again)
+    assert _true_resid(dims, U, 0.1, b, to_host(x)) <= 1.01e-8
+    assert rel_err_2(to_host(x), xr) <= 1e-6
