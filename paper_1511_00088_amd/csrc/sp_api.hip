@@ -715,7 +715,7 @@ int solve_impl(int nsys, const sp_system* systems, const sp_cg_params* prm, sp_c
     int rc = make_layout(nsys, systems, prm, batched ? NB : 1, &L);
     if (rc) return rc;
     if (batched && many_systems(nsys, systems, prm)) {
-        // a workspace that holds the groups but not this layout (at most a few KB more) keeps the groups
+        // a workspace that holds the groups but not this layout (some KB more on the smallest lattices) keeps the groups
         Layout M;
         if ((rc = make_layout(nsys, systems, prm, 1, &M, true))) return rc;
         if (ws_bytes >= M.total) L = M;
