@@ -22,7 +22,10 @@ struct LaunchCfg {
 // 2.45 against 2.86 (recon 18) and 2.78 against 3.48 (FP64); 20,736 sites 3.22 against 3.59, 3.49 against 3.37 and 4.44
 // against 4.38; 32,768 sites 2.78 against 2.90 (recon 12) and 2.55 against 2.91 (fixed-point links); 65,536 sites 5.45
 // against 4.55 (recon 12), where the chip is full without it. FP32 recon 18 and FP64 move the most bytes a site and turn
-// first. FP16 and BF16 vectors keep a lane per site: the order of a site's eight terms decides how their last digits round,
+// first. With the block sizes of solve_threads on both sides (m = 0.1) the line stays: 8,000 sites 1.79 against 2.25
+// (recon 12), 1.78 against 1.94 (recon 18) and 1.85 against 2.23 (FP64); 10,368 sites 1.89 against 2.12, 1.96 against 1.86
+// and 2.17 against 2.09; 30,720 sites 2.54 against 2.58 (recon 12), 2.48 against 3.09 (recon 8); 65,536 sites 4.65
+// against 4.30 (recon 8). FP16 and BF16 vectors keep a lane per site: the order of a site's eight terms decides how their last digits round,
 // and with it, by some percent either way, where such a solve's reliable updates fall.
 inline bool quad_lanes(int Vh, int lp, int recon, int vp) {
     if (vp != F32 && vp != F64) return false;
