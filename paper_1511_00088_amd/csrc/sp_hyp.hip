@@ -414,7 +414,12 @@ __device__ __forceinline__ void poly_mul(const double (&a)[3], const double (&b)
 //   v^2 = 3 + e2 + 2 u w; u is the root next to its series start, by Newton's steps with a fixed slope (the
 //   derivative 2 (u v - w) is the product of the eigenvalues' pairwise sums, so the root is well conditioned);
 //   G = (1 + E)^-1/2 follows from the characteristic polynomial P^3 = u P^2 - v P + w (Hasenfratz, Hoffmann and
-//   Schaefer, JHEP 0705 (2007) 029, give the coefficients), and G^2 = (1 + E)^-1 from that of 1 + E;
+//   Schaefer, JHEP 0705 (2007) 029, give the coefficients of 1, P^2 and P^4): in 1, E and E^2 they are
+//   [u (1 + e2) + w (2 + v)] / (w (u v - w)), -(u + w) / (w (u v - w)) and u / (w (u v - w)). u, v and w are carried as
+//   their departures du, dv and k from 3, 3 and 1, and the first coefficient as its departure from 1, so that rounding
+//   shrinks with E: formed from u, v and w themselves, 1 is what is left of sums of 27, and the links came out 1.6e-15
+//   (rms over a link) from the maximiser in place of 2.6e-16;
+//   G^2 = (1 + E)^-1 follows from the characteristic polynomial of 1 + E;
 //   exp(i Theta) = (1 - Y^2)^1/2 + i Y, so only the even part needs a series.
 // mu solves tr asin(mu G) = -phi, by fixed-point steps from -phi / tr G that gain a factor of about 2 / Y^2 each.
 // The series run to Y^5 (Y at most 1e-3 in norm: omitted terms below 1e-19), or to Y^13 in the lanes that need it.
@@ -449,19 +454,21 @@ __device__ __forceinline__ bool proj_direct(const M3& w, M3& x) {
     const C o = cmul(o01, o12);
     const double e2 = -0.5 * t2, e3 = dg[0] * dg[1] * dg[2] + 2.0 * (o.re * o02.re + o.im * o02.im) - dg[0] * n12 -
                                       dg[1] * n02 - dg[2] * n01;
-    const double c3 = 1.0 + e2 + e3, rww = rsq(c3), ww = c3 * rww, rc3 = rww * rww;
-    double u = 3.0 - t2 * (0.125 + t2 * (5.0 / 256.0)) + e3 * (3.0 / 16.0);
-    const double slope = __builtin_amdgcn_rcp(u * (u * u - 3.0) - 2.0 * ww);
+    // w = 1 + k, u = 3 + du, v = 3 + dv
+    const double c = e2 + e3, c3 = 1.0 + c, rww = rsq(c3), ww = c3 * rww, rc3 = rww * rww;
+    const double k = c * rcp(1.0 + ww), rhs = e2 + 6.0 * k, lin = 16.0 - 2.0 * k;
+    double du = -t2 * (0.125 + t2 * (5.0 / 256.0)) + e3 * (3.0 / 16.0), dv = du * (3.0 + 0.5 * du);
+    const double slope = __builtin_amdgcn_rcp(lin + 6.0 * du + 2.0 * dv * (3.0 + du));
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
-        const double hv = 0.5 * (u * u - 3.0);
-        u -= (hv * hv - (3.0 + e2) - 2.0 * u * ww) * slope;
+        du -= (du * (lin + 3.0 * du) + dv * dv - rhs) * slope;
+        dv = du * (3.0 + 0.5 * du);
     }
-    const double v = 0.5 * (u * u - 3.0), uv = u * v;
-    const double rden = rww * rcp(uv - ww);
-    const double f0 = (uv * v - ww * (u * u + v)) * rden, f1 = (2.0 * uv - ww - u * u * u) * rden, f2 = u * rden;
+    const double sum = du + dv, prod = du * dv, u = 3.0 + du;
+    const double rden = rww * rcp(8.0 + (3.0 * sum + prod - k));  // 1 / (w (u v - w))
+    const double n0 = 3.0 * e2 - 2.0 * (sum + k) + (du * e2 - prod) + k * (k - 3.0 * sum + dv - prod);
     const double h[3] = {(1.0 + e2) * rc3, -rc3, rc3};  // (1 + E)^-1
-    double g0[3] = {f0 + f1 + f2, f1 + 2.0 * f2, f2}, g1[3], g2[3];
+    double g0[3] = {1.0 + n0 * rden, -(u + ww) * rden, u * rden}, g1[3], g2[3];
     poly_mul(g0, h, e2, e3, g1);
     poly_mul(g1, h, e2, e3, g2);
     const C d = det3(w);
@@ -578,6 +585,18 @@ __device__ __noinline__ void proj_iterate(double2* m) {
             }
         if (diff2 <= 1e-30) break;
     }
+    // every sweep rounds; X (3 - X^dag X) / 2 leaves of X^dag X - 1 (1e-14 after many) its square, so that row 2 may be
+    // rebuilt from the others (row2)
+    M3 n = mul_dn_rows<3>(x, x);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) n.e[i][j] = {0.5 * ((i == j ? 1.0 : 0.0) - n.e[i][j].re), -0.5 * n.e[i][j].im};
+    const M3 dx = mul_rows<3>(x, n);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) x.e[i][j] = cadd(x.e[i][j], dx.e[i][j]);
     put(x);
 }
 

@@ -58,6 +58,60 @@ def test_hyp_blocks_and_projection_branches(dims, eps):
     assert np.max(np.abs(_gpu_hyp(dims, U) - hyp.hyp_smear(dims, U))) <= 1e-12
 
 
+def _maximiser_80bit(W, start):
+    """The SU(3) maximiser of Re tr(X^dag W) in 80-bit numpy: Newton-Schulz steps make the start unitary, the cube root of
+    its determinant is divided out, and SU(2)-subgroup sweeps run until they move nothing that 64 bits could show."""
+    X = start.astype(np.clongdouble)
+    for _ in range(3):
+        X = 0.5 * (3 * X - X @ hyp.dag(X) @ X)
+    c = np.cross(X[..., 1, :], X[..., 2, :])
+    d = np.sum(X[..., 0, :] * c, axis=-1)
+    X = X * np.exp(-1j * (np.arctan2(d.imag, d.real) / 3))[..., None, None]
+    for _ in range(200):
+        Y = X
+        for i, j in ((0, 1), (0, 2), (1, 2)):
+            Y = hyp.su2_step(Y, W, i, j)
+        if np.max(np.abs(Y - X)) < 1e-18:
+            return Y
+        X = Y
+    raise AssertionError("the 80-bit sweeps did not settle")
+
+
+@pytest.mark.parametrize("eps", [0.02, 0.3, 0.6])
+def test_projection_is_as_exact_as_its_arithmetic(eps):
+    """Weights (0.75, 0, 0): levels 1 and 2 project the links themselves, level 3 one staple sum per link, formed here in
+    80 bits. Rounding alone: the sum, F of X = W F and their product round each entry some ten times by up to 2^-54 of
+    values up to 1 (rms 2^-54 / sqrt(3) each, 1e-16 in all), so an rms over a link's nine entries (Frobenius) of 3 x 1e-16,
+    and a little more through rows rebuilt from the others; 8e-16 is asked, and 2e-15 of the worst entry."""
+    dims, a1 = (6, 4, 4, 8), 0.75
+    announce(f"hyp projection error eps={eps}")
+    U = li.near_identity_links(dims, eps, 457)
+    V = _gpu_hyp(dims, U, (a1, 0.0, 0.0)).astype(np.clongdouble)
+    # the links the levels start from: U projected (its own rounding would otherwise count as the kernel's)
+    P = _maximiser_80bit(U.astype(np.clongdouble), U)
+    W = [(1 - np.longdouble(a1)) * U[mu].astype(np.clongdouble) + np.longdouble(a1) / 6 *
+         sum(hyp.staples(P[nu], P[mu], mu, nu, dims) for nu in range(4) if nu != mu) for mu in range(4)]
+    for mu in range(4):
+        err = np.abs(V[mu] - _maximiser_80bit(W[mu], hyp.polar_start(W[mu].astype(np.complex128))))
+        rms = float(np.sqrt(np.mean(np.sum(err * err, axis=(-2, -1)))))
+        announce(f"  mu={mu} rms={rms:.2e} max={float(err.max()):.2e}")
+        assert rms <= 8e-16 and err.max() <= 2e-15, mu
+
+
+@pytest.mark.parametrize("eps,alpha", [(0.05, hyp.HYP_ALPHA), (0.3, hyp.HYP_ALPHA), (1.0, hyp.HYP_ALPHA), (1.4, hyp.HYP_ALPHA),
+                                       (0.3, (0.5, 0.3, 0.9))])
+def test_smeared_links_are_unitary_to_rounding(eps, alpha):
+    """V V^dag - 1 holds each entry's error of a link (about 3e-16, see above) twice: rms over a link below 1.5e-15, the
+    worst of some 100,000 entries below 3.5e-15; with the short series, the long one and, past eps 0.7, the iterations."""
+    dims = (6, 8, 6, 10)
+    announce(f"hyp unitarity eps={eps} alpha={alpha}")
+    V = _gpu_hyp(dims, li.near_identity_links(dims, eps, 458), alpha).astype(np.clongdouble)
+    D = np.abs(V @ hyp.dag(V) - np.eye(3))
+    rms = float(np.sqrt(np.mean(np.sum(D * D, axis=(-2, -1)))))
+    announce(f"  rms={rms:.2e} max={float(D.max()):.2e}")
+    assert rms <= 1.5e-15 and D.max() <= 3.5e-15
+
+
 def test_largest_weights_on_haar_links_ill_conditioned_maximum():
     # weights (1, 1, 1) on Haar links give staple sums whose determinant phase sits at +-pi; there the
     # maximiser of Re tr(X^dag W) lies along a nearly flat direction and the SU(2)-subgroup sweeps converge
