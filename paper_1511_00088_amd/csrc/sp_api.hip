@@ -268,6 +268,7 @@ struct GroupPlan {
     Geom g;
     const sp_gauge* U;
     std::vector<int> sys;  // indices into the caller's system list
+    int field = 0;         // number of its gauge field and geometry, in the order of the list
     int nblk = 0, blk0 = 0, bundle = 1;
     size_t partials_off = 0, partials_p_off = 0, partials_r_off = 0, rec_off = 0;
 };
@@ -299,6 +300,18 @@ size_t sys_block_bytes(int Vh, int inner, size_t slot_off[NSLOT]) {
     return off;
 }
 
+// The links and geometry that a system must share with another to share its link loads, as bytes.
+std::string field_key(const sp_gauge& U, const Geom& g) {
+    std::string k;
+    auto add = [&](const auto& v) { k.append((const char*)&v, sizeof v); };
+    add(U.f64);
+    add(U.lo);
+    add(U.recon);
+    add(U.lo_prec);
+    add(g);
+    return k;
+}
+
 // Whether the systems of a batched solve iterate as single systems in common launches (DescMany) instead of in groups that
 // share their link loads: small lattices, whose five launches an iteration are bound by latency.
 bool many_systems(int nsys, const sp_system* systems, const sp_cg_params* prm) {
@@ -325,29 +338,29 @@ int make_layout(int nsys, const sp_system* systems, const sp_cg_params* prm, int
     L->inner = prm->inner;
     L->nbatch_rhs = n_rhs_max;
     L->groups.clear();
+    std::map<std::string, std::pair<int, int>> fields;  // gauge field and geometry -> its number, its last group
     for (int i = 0; i < nsys; ++i) {
         const sp_system& s = systems[i];
         Geom g;
         int rc = check_geom(s.g, &g);
         if (rc) return rc;
         if (!s.U) return fail(SP_ERR_INVALID_ARG, "system %d: gauge is null", i);
-        int gi = -1;
-        for (size_t k = 0; k < L->groups.size(); ++k) {
-            GroupPlan& G = L->groups[k];
-            if ((int)G.sys.size() < n_rhs_max && G.U->f64 == s.U->f64 && G.U->lo == s.U->lo &&
-                G.U->recon == s.U->recon && G.U->lo_prec == s.U->lo_prec && !memcmp(&G.g, &g, sizeof g)) {
-                gi = (int)k;
-                break;
+        GroupPlan G;
+        G.g = g;
+        G.U = s.U;
+        std::pair<int, int>* f = nullptr;
+        if (!many) {  // many: a group per system, in the caller's order
+            f = &fields.try_emplace(field_key(*s.U, g), std::make_pair((int)fields.size(), -1)).first->second;
+            G.field = f->first;
+            // a field's groups fill one after the other, so only its last one can have room
+            if (f->second >= 0 && (int)L->groups[f->second].sys.size() < n_rhs_max) {
+                L->groups[f->second].sys.push_back(i);
+                continue;
             }
+            f->second = (int)L->groups.size();
         }
-        if (gi < 0) {
-            GroupPlan G;
-            G.g = g;
-            G.U = s.U;
-            L->groups.push_back(G);
-            gi = (int)L->groups.size() - 1;
-        }
-        L->groups[gi].sys.push_back(i);
+        G.sys.push_back(i);
+        L->groups.push_back(std::move(G));
     }
     // launch shape: the tuned block size of the largest group's operator
     int big = 0;
@@ -366,24 +379,15 @@ int make_layout(int nsys, const sp_system* systems, const sp_cg_params* prm, int
             L->cfg.nt = solve_threads(L->cfg.quad ? 4 * G.g.Vh : G.g.Vh);
         if (many) L->cfg.stream = 0;
     }
-    // Groups of one gauge field stand in a row (bundles of up to BUNDLE) and share a first block: their blocks alternate.
-    auto same_field = [](const GroupPlan& a, const GroupPlan& b) {
-        return a.U->f64 == b.U->f64 && a.U->lo == b.U->lo && a.U->recon == b.U->recon && a.U->lo_prec == b.U->lo_prec &&
-               !memcmp(&a.g, &b.g, sizeof a.g);
-    };
-    for (size_t i = 0; i < L->groups.size() && !many; ++i) {
-        size_t at = i + 1;
-        for (size_t k = i + 1; k < L->groups.size(); ++k)
-            if (same_field(L->groups[i], L->groups[k])) {
-                std::rotate(L->groups.begin() + at, L->groups.begin() + k, L->groups.begin() + k + 1);
-                ++at;
-            }
-        i = at - 1;
-    }
+    // Groups of one gauge field stand in a row, fields in the order of their first system (bundles of up to BUNDLE), and
+    // share a first block: their blocks alternate.
+    if (!many)
+        std::stable_sort(L->groups.begin(), L->groups.end(),
+                         [](const GroupPlan& a, const GroupPlan& b) { return a.field < b.field; });
     int blk = 0;
     for (size_t i = 0; i < L->groups.size();) {
         size_t n = 1;
-        while (n < BUNDLE && i + n < L->groups.size() && same_field(L->groups[i], L->groups[i + n])) ++n;
+        while (!many && n < BUNDLE && i + n < L->groups.size() && L->groups[i].field == L->groups[i + n].field) ++n;
         for (size_t k = i; k < i + n; ++k) {
             GroupPlan& G = L->groups[k];
             G.nblk = blocks_for(L->cfg.quad ? 4 * G.g.Vh : G.g.Vh, L->cfg.nt);

@@ -276,3 +276,29 @@ def test_noalloc_force_refuses_lattices_beyond_its_array():
     small = sp.Lattice((4, 4, 4, 4))
     assert lib.sp_cg_force_noalloc(ctypes.byref(small.geom), None, 0.1, None, None, None, None, None,
                                    None) == _lib.SP_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("one_field", [True, False])
+def test_batch_layout_grows_with_the_number_of_systems(one_field):
+    """The layout of a batch (the workspace query's work, and each solve's) takes time in proportion to its systems, not
+    to their square: four times the systems in less than eight times the time, best of five."""
+    import time
+
+    lib = _lib.load()
+    lat = sp.Lattice((2, 2, 2, 2))
+    prm = _lib.sp_cg_params(1e-8, 1000, _lib.SP_F32, 0.1, 0, 0, 0, 1)
+
+    def query(n):
+        fields = [_lib.sp_gauge(0x10000 + 0x1000 * k, 0x90000000 + 0x1000 * k, _lib.SP_F32, 12)
+                  for k in range(1 if one_field else n)]
+        arr = (_lib.sp_system * n)()
+        for k in range(n):
+            arr[k] = _lib.sp_system(ctypes.pointer(lat.geom), ctypes.pointer(fields[k % len(fields)]), 0.1, 0x1000, 0x2000)
+        best = float("inf")
+        for _ in range(5):
+            t0 = time.perf_counter()
+            assert lib.sp_cg_workspace_bytes(n, arr, ctypes.byref(prm)) > 0
+            best = min(best, time.perf_counter() - t0)
+        return best
+
+    assert query(16000) < 8 * query(4000)
