@@ -357,3 +357,124 @@ def test_small_batches_iterate_as_single_systems(dims, n, inner, recon, lo):
         alone, st1 = sp.cg_solve(g, m, b, tol=1e-10, inner=inner)
         assert st[k].converged and (st[k].iters, st[k].reliable_updates) == (st1.iters, st1.reliable_updates), k
         assert torch.equal(xs[k], alone) and torch.equal(xs[k], again[k]), k
+
+
+# ---- groups of small lattices ----------------------------------------------------------------------------
+# Systems of one small extent iterate as single systems, so a batch forms groups of them only beside a system of another
+# extent.
+OTHER = (4, 4, 4, 6)
+
+
+def _other_extent(seed=77):
+    U = li.near_identity_links(OTHER, 0.3, seed)
+    return gauge(OTHER, U, "f32", 12), 0.1, to_dev(li.gaussian_even_source(OTHER, seed + 1))
+
+
+def test_bundles_across_the_64_groups_of_one_ballot():
+    """62 fields of one system, then one of 20 (five groups, 62 to 66: a bundle of four across lane 64 of the block lookup,
+    and a bundle of one), three more fields of one system, and a last lattice of another extent: every system of the bundles
+    and the others around lane 64 against the oracle."""
+    dims = (4, 4, 4, 4)
+    announce("bundles across the first 64 groups")
+    systems, host = [], []
+
+    def add(U, n, seed):
+        G = gauge(dims, U, "f32", 12)
+        for k in range(n):
+            b, m = li.gaussian_even_source(dims, seed + k), 0.05 + 0.002 * k
+            systems.append((G, m, to_dev(b)))
+            host.append((U, m, b))
+
+    for i in range(62):
+        add(li.near_identity_links(dims, 0.3, 1500 + i), 1, 1600 + i)
+    add(li.near_identity_links(dims, 0.3, 1700), 20, 1710)
+    for i in range(3):
+        add(li.near_identity_links(dims, 0.3, 1750 + i), 1, 1760 + i)
+    xs, stats = sp.cg_solve_batched(systems + [_other_extent()], tol=1e-9)
+    assert all(s.converged for s in stats)
+    for k in [0, 31, *range(58, 85)]:
+        U, m, b = host[k]
+        assert rel_err_2(to_host(xs[k]), oracle.cg_solve(dims, U, m, b, tol=1e-12)[0]) <= 1e-7, k
+
+
+@pytest.mark.parametrize("inner", ["f32", "f64"])
+def test_systems_of_one_group_stop_by_themselves(inner):
+    """Groups of four right-hand sides on one small field (nine systems: two full groups and one of one): masses two decades
+    apart, a zero source, and a source with a NaN. Each system ends as it does alone in a group: the zero one at x = 0
+    without an iteration, the broken one by its own status, the others with a residual of 1e-9 in the oracle's operator."""
+    from paper_1511_00088_amd import _lib as L
+
+    dims = (4, 4, 4, 8)
+    announce(f"group of small systems {inner}")
+    U = li.near_identity_links(dims, 0.3, 1800)
+    G = gauge(dims, U, inner, 12 if inner == "f32" else 18)
+    go = gauge(OTHER, li.near_identity_links(OTHER, 0.3, 77), inner, 12 if inner == "f32" else 18)
+    bs = [li.gaussian_even_source(dims, 1801 + k) for k in range(9)]
+    bs[2] = 0.0 * bs[2]
+    bs[5] = bs[5].copy()
+    bs[5][7, 1] = np.nan
+    ms = [0.01 * 100.0 ** (k / 8) for k in range(9)]
+    xs, st = sp.cg_solve_batched([(G, m, to_dev(b)) for m, b in zip(ms, bs)] +
+                                 [(go, 0.1, to_dev(li.gaussian_even_source(OTHER, 78)))], tol=1e-9, inner=inner,
+                                 raise_on_breakdown=False)
+    assert st[5].status == L.SP_ERR_BREAKDOWN and not st[5].converged
+    assert st[2].converged and st[2].iters == 0 and not bool(xs[2].abs().max())
+    for k in (0, 1, 3, 4, 6, 7, 8):
+        assert st[k].converged
+        assert _true_resid_oracle(dims, U, ms[k], bs[k], to_host(xs[k])) <= 1.01e-9, k
+
+
+def test_iteration_cap_in_groups():
+    dims = (4, 4, 4, 8)
+    announce("iteration cap in groups")
+    U = li.near_identity_links(dims, 0.3, 1820)
+    G = gauge(dims, U, "f32", 12)
+    sysl = [(G, m, to_dev(li.gaussian_even_source(dims, 1821 + k))) for k, m in enumerate([0.01, 0.02, 2.0, 0.05, 0.01])]
+    xs, st = sp.cg_solve_batched(sysl + [_other_extent()], tol=1e-10, max_iter=20)
+    assert st[2].converged and st[2].iters < 20
+    for k in (0, 1, 3, 4):
+        assert not st[k].converged and st[k].iters == 20
+        r = _true_resid_oracle(dims, U, sysl[k][1], to_host(sysl[k][2]), to_host(xs[k]))
+        assert abs(r - st[k].true_rel_resid) <= 1e-9 + 1e-6 * r
+
+
+def test_small_batch_in_the_workspace_of_its_groups():
+    """Lattices of a few sites need some KB more to iterate as single systems than in groups. A workspace that holds the
+    groups alone is taken, and keeps them; one byte less is refused before anything runs."""
+    import ctypes
+
+    from paper_1511_00088_amd import _lib as L
+
+    dims, n = (4, 4, 4, 4), 8
+    announce("workspace of the groups")
+    U = li.near_identity_links(dims, 0.3, 1840)
+    G = gauge(dims, U, "f32", 12)
+    bs = [li.gaussian_even_source(dims, 1841 + k) for k in range(n)]
+    bd, xs = [to_dev(b) for b in bs], [torch.empty(128, 3, dtype=torch.complex128, device="cuda:0") for _ in bs]
+    arr = (L.sp_system * n)()
+    for k in range(n):
+        arr[k] = L.sp_system(ctypes.pointer(G.lat.geom), ctypes.pointer(G.struct), 0.05, bd[k].data_ptr(), xs[k].data_ptr())
+    prm = L.sp_cg_params(1e-9, 100000, L.SP_F32, 0.1, 0, 0, 0, 1)
+    lib = L.load()
+    asked = lib.sp_cg_workspace_bytes(n, arr, ctypes.byref(prm))
+    ws = torch.empty(asked, dtype=torch.uint8, device="cuda:0")
+    st = (L.sp_cg_stats * n)()
+
+    def solve(nbytes):
+        for x in xs:
+            x.fill_(float("nan"))
+        return lib.sp_cg_solve_batched(n, arr, ctypes.byref(prm), st, ws.data_ptr(), nbytes,
+                                       torch.cuda.current_stream().cuda_stream)
+
+    lo, hi = 0, asked  # refused, taken
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        rc = solve(mid)
+        assert rc in (L.SP_OK, L.SP_ERR_WORKSPACE)
+        lo, hi = (mid, hi) if rc == L.SP_ERR_WORKSPACE else (lo, mid)
+    assert hi < asked
+    for nbytes in (hi, asked):
+        assert solve(nbytes) == L.SP_OK
+        for k in range(n):
+            assert st[k].converged
+            assert rel_err_2(to_host(xs[k]), oracle.cg_solve(dims, U, 0.05, bs[k], tol=1e-12)[0]) <= 1e-7
