@@ -199,8 +199,14 @@ int sp_cg_solve(const sp_geom* g, const sp_gauge* U, double mass, const double* 
  * field share each link load, and independent systems are the unit that spreads over GPUs without communication.
  * Solve nsys independent systems together: systems sharing a gauge field and geometry form groups of up
  * to 4 right-hand sides; all groups advance in one launch per kernel, captured in a hipGraph per chunk
- * of iterations (FP32 and FP64 systems of one small geometry, up to some 400,000 sites per parity in all, advance
- * in common launches without forming groups, with the launch shape of single solves); converged systems stop updating while the others continue. Groups may differ in volume
+ * of iterations; converged systems stop updating while the others continue. Two or more FP32 or FP64 systems that all
+ * have one geometry (extents and time boundary), link precision and recon, with up to 400,000 sites per parity in all
+ * (262,144 where vectors or links are not FP32), form no groups: each iterates as a single system does, in common
+ * launches. One system of another geometry or packing in the list, and the batch is one of groups again; so is a batch
+ * of one system. A system's solution is the one sp_cg_solve gives it, bit for bit, where both take the same lanes per
+ * site, a choice that goes by the sites of all systems (up to 32,768 four lanes; 8,192 with FP64 vectors or FP32
+ * recon-18 links), and the same iterations between residual checks (poll_chunk given, or less than 65,536 sites a
+ * system); otherwise it differs by rounding. Groups may differ in volume
  * and time boundary; a zero b_e stops at the first residual check with x_e = 0. stats: host array of nsys
  * (nullable). Returns SP_OK if every system converged, SP_NOT_CONVERGED if any did not, or an error. When
  * some systems break down (SP_ERR_BREAKDOWN), stats[i].status names them and the other systems' x_e and

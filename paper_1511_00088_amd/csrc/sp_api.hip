@@ -373,6 +373,9 @@ int make_layout(int nsys, const sp_system* systems, const sp_cg_params* prm, int
         L->cfg = n_rhs_max > 1 ? tuned_cfg_batched(G.g, lp, rc, prm->inner) : tuned_cfg_solve(G.g, lp, rc, prm->inner);
         // one system: the fused iteration's block size (solve_threads) whenever 256 threads admit that iteration; the
         // block order and the link-load policy stay the tuned ones
+        // (many: the lanes go by the sites of all systems, which share the chip. By each system's own, batches whose total is
+        // just past the limit gain up to 9%, larger ones lose: 3 on 12^3x24 3.0 -> 3.6 ms, 12 5.2 -> 10.2, 128 on 8^4
+        // 6.6 -> 11.0. So a system's summation order depends on the size of its batch.)
         const int sites = many ? nsys * G.g.Vh : G.g.Vh;
         L->cfg.quad = n_rhs_max == 1 && quad_lanes(sites, lp, rc, prm->inner);
         if (n_rhs_max == 1 && blocks_for(G.g.Vh, 256) <= FUSED_PARTIALS * 256)

@@ -478,3 +478,27 @@ def test_small_batch_in_the_workspace_of_its_groups():
         for k in range(n):
             assert st[k].converged
             assert rel_err_2(to_host(xs[k]), oracle.cg_solve(dims, U, 0.05, bs[k], tol=1e-12)[0]) <= 1e-7
+
+
+@pytest.mark.parametrize("dims,n,inner,recon", [
+    ((8, 8, 8, 8), 4, "f32", 18),   # 8,192 sites in all: four lanes a site, as each system alone
+    ((8, 8, 8, 8), 5, "f32", 18),   # 10,240: a lane a site, where each system alone takes four
+    ((8, 8, 8, 8), 5, "f64", 18),
+    ((8, 8, 16, 16), 4, "f32", 12),  # 32,768
+    ((8, 8, 16, 16), 5, "f32", 12),  # 40,960
+])
+def test_small_batches_either_side_of_four_lanes_per_site(dims, n, inner, recon):
+    """The lanes a site of a small batch go by the sites of all its systems. Up to the limit each system's solution is the
+    one it has alone, bit for bit; past it the operator's terms add in another order, and each is within the solve's own
+    tolerance of the oracle's."""
+    announce(f"small batch {dims} x {n} {inner} r{recon}")
+    U = li.near_identity_links(dims, 0.3, 1860)
+    G = gauge(dims, U, inner, recon)
+    bs = [li.gaussian_even_source(dims, 1861 + k) for k in range(n)]
+    xs, st = sp.cg_solve_batched([(G, 0.1, to_dev(b)) for b in bs], tol=1e-9, inner=inner)
+    limit = 8192 if inner == "f64" or recon == 18 else 32768
+    for k in (0, n - 1):
+        assert st[k].converged
+        if n * G.lat.Vh <= limit:
+            assert torch.equal(xs[k], sp.cg_solve(G, 0.1, to_dev(bs[k]), tol=1e-9, inner=inner)[0])
+        assert rel_err_2(to_host(xs[k]), oracle.cg_solve(dims, U, 0.1, bs[k], tol=1e-12)[0]) <= 1e-7
