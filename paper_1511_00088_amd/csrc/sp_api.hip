@@ -182,17 +182,21 @@ std::string tune_key(const Geom& g, int lp, int recon, int vp) {
 // Launch shapes of lattices that the table does not hold, by size; measured on ten untuned lattices of 6,000 to 813,824
 // sites per parity.
 //  - The stand-alone operator: 64-thread blocks, which even out a last round of blocks (FP64 on 138,600 sites, two blocks
-//    of 256 a CU and a remainder: 31.4 against 35.7 us; never more than 3% slower). Links of 96 MB or more stream past the
-//    caches: a field of that size does not stay in the 256 MB Infinity Cache between two calls of a program that does
-//    anything else in between. Cold calls at 20^3x64: FP32 recon 12 (98 MB) 20.5 against 23.9 us, FP64 (295 MB) 56.7
-//    against 61.7; back to back on one field 18.9 against 17.9. Below, cached loads win cold too (recon 18 on 138,600
-//    sites, 80 MB: 15.1 against 15.5 us; fixed point on 331,776, 64 MB: 15.5 against 18.2).
-//  - A single solve, whose launches follow one another on one field: 256-thread blocks (the fused iteration's partials) and
-//    streaming only where the field exceeds the Infinity Cache by itself: at 225 MB (recon 12) 10.55 ms cached against
-//    11.98, at 290 (recon 18) 13.0 against 13.2, at 312 (recon 12) 16.8 against 16.3, at 382 (FP64) 16.9 against 15.7.
+//    of 256 a CU and a remainder: 31.4 against 35.7 us; never more than 3% slower).
+//  - The stand-alone operator and a single solve: link loads that stream past the caches where the field alone exceeds the
+//    256 MB Infinity Cache. A field that fits is served from there by the next application (an eigensolver's, a
+//    polynomial's, an iteration's), which streaming gives away; a larger one only pushes out what else would hit. The operator,
+//    cached against streaming (us), repeated on one field and after a flush of the cache: 98 MB 17.7, 18.7 and 22.7, 21.1;
+//    127 MB 22.7, 24.4 and 28.3, 26.7; 160 MB (FP64) 26.7, 29.4 and 33.0, 32.2; 209 MB 35.6, 42.1 and 46.5, 44.3; 255 MB 40.9,
+//    46.6 and 51.6, 49.2; 283 MB 56.1, 60.0 and 65.8, 63.1; 295 MB (FP64) 53.0, 55.3 and 59.1, 57.8; 302 MB (FP16) 57.5,
+//    53.7 and 60.8, 56.4; 337 MB 71.3, 67.5 and 74.8, 70.6; 405 MB 85.1, 78.1 and 87.4, 82.5: from 300 MB streaming
+//    wins both ways, below it costs the repeated call 1 to 22% to save a cold one 2 to 7%. A solve: at 225 MB (recon 12)
+//    10.55 ms cached against 11.98, at 290 (recon 18) 13.0 against 13.2, at 312 (recon 12) 16.8 against 16.3, at 382
+//    (FP64) 16.9 against 15.7.
+//  - A single solve has 256-thread blocks (the fused iteration's partials, where that applies: solve_threads).
 //  - A batch: 64-thread blocks up to 40,000 sites (6,000 sites, three systems: 3.81 against 4.16 ms; 32,256: 4.23 against
 //    4.44), 256 beyond (63,360 sites, six systems: 6.09 against 6.19; 230,400: 16.4 against 16.7).
-size_t link_field_bytes(const Geom& g, int lp, int recon) { return 8 * (size_t)g.Vh * link_bytes(lp, recon); }
+bool links_stream(const Geom& g, int lp, int recon) { return 8 * (size_t)g.Vh * link_bytes(lp, recon) >= 300000000; }
 
 bool find_cfg(const std::string& key, LaunchCfg* c) {
     auto it = g_tune.find(key);
@@ -204,7 +208,7 @@ LaunchCfg tuned_cfg(const Geom& g, int lp, int recon, int vp) {
     LaunchCfg c;
     if (find_cfg(tune_key(g, lp, recon, vp), &c)) return c;
     c.nt = 64;
-    c.stream = link_field_bytes(g, lp, recon) >= 96000000;
+    c.stream = links_stream(g, lp, recon);
     return c;
 }
 
@@ -223,7 +227,7 @@ LaunchCfg tuned_cfg_solve(const Geom& g, int lp, int recon, int vp) {
     LaunchCfg c;
     const std::string key = tune_key(g, lp, recon, vp);
     if (find_cfg(key + "/solve", &c) || find_cfg(key, &c)) return c;
-    c.stream = link_field_bytes(g, lp, recon) >= 300000000;
+    c.stream = links_stream(g, lp, recon);
     return c;
 }
 
