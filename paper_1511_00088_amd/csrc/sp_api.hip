@@ -1170,14 +1170,14 @@ int sp_tune_dslash(const sp_geom* g, const sp_gauge* U, int prec, void* in, void
     HIP_TRY(hipEventCreate(&ev.a));
     HIP_TRY(hipEventCreate(&ev.b));
     hipEvent_t e0 = ev.a, e1 = ev.b;
-    const int nts[3] = {64, 128, 256};
+    const std::vector<int> all_nts = {64, 128, 256};
     const int reps = 10, trials = 5;
     const int use64 = prec == SP_F64;
-    // For every block size, block order and (for the one-right-hand-side operator) link-load policy: 3 warm-up
+    // For every block size, block order and (for the one-right-hand-side operator) link-load policy asked: 3 warm-up
     // launches, then `trials` timings of `reps` back-to-back launches; the median trial's time per launch
     // counts and the fastest configuration wins. Back-to-back launches are the solver's situation (a link field
     // that fits in the Infinity Cache stays there between the iteration's launches).
-    auto sweep = [&](auto launch, bool policies, LaunchCfg* best, float* best_t) -> hipError_t {
+    auto sweep = [&](auto launch, const std::vector<int>& nts, bool policies, LaunchCfg* best, float* best_t) -> hipError_t {
         *best_t = 1e30f;
         for (int stream_links = 0; stream_links <= (policies ? 1 : 0); ++stream_links)
             for (int remap = 0; remap <= 1; ++remap)
@@ -1209,13 +1209,16 @@ int sp_tune_dslash(const sp_geom* g, const sp_gauge* U, int prec, void* in, void
     };
     LaunchCfg best, best4;
     float best_t = 0, best4_t = 0;
+    // Four lanes per site have one block size and load links one way (dslash_shape): only the block order is timed there.
+    // The entry then holds the block size and policy of an untuned lattice, which a shard of these extents reads.
+    const bool quad = quad_lanes(G.Vh, lp, recon, prec);
     HIP_TRY(sweep(
         [&](LaunchCfg c) {
             const int nb = dslash_shape(G.Vh, lp, recon, prec, &c);
             d.grp.nblk = nb;
             return launch_dslash(d, nb, c, lp, recon, prec, 1, S_P, S_T, DS_PLAIN, G_NONE, use64, s);
         },
-        true, &best, &best_t));
+        quad ? std::vector<int>{64} : all_nts, !quad, &best, &best_t));
     // The NB-right-hand-side operator of batched solves has its own register use and therefore its own
     // best shape (key suffix "/n4"). It is timed on NB copies of the input into NB outputs, in a temporary
     // device buffer that also holds the group and system descriptors; the buffer is freed before return.
@@ -1256,7 +1259,7 @@ int sp_tune_dslash(const sp_geom* g, const sp_gauge* U, int prec, void* in, void
                     }
                     return launch_dslash(db, nb, c, lp, recon, prec, 1, S_P, S_T, DS_PLAIN, G_NONE, use64, s);
                 },
-                false, &best4, &best4_t);
+                all_nts, false, &best4, &best4_t);
         const hipError_t es = hipStreamSynchronize(s);
         (void)hipFree(buf);
         HIP_TRY(e);

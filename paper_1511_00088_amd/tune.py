@@ -97,8 +97,8 @@ def _links(dims, device, seed=5):
 
 def tune_solves(dims_list, combos=SOLVE_COMBOS, device="cuda:0", iters=75, reps=3):
     """Block order and link-load policy of the single-system solve, timed on the solve itself: a solve of `iters`
-    iterations (m = 0.01, tol far below reach) per configuration, 256-thread blocks (what the fused iteration
-    takes), the fastest per iteration kept as the "/solve" entry."""
+    iterations (m = 0.01, tol far below reach) per configuration, the fastest per iteration kept as the "/solve" entry.
+    Its block size is read only where a lattice is too large for the fused iteration, which takes its own."""
     import time
 
     chosen = {}

@@ -269,3 +269,24 @@ def test_untuned_link_loads_suit_a_field_applied_again_and_again(dims):
         pinned.append(us())
     announce(f"  untuned {untuned:.1f} us, cached {pinned[0]:.1f}, streaming {pinned[1]:.1f}")
     assert untuned <= 1.08 * min(pinned)
+
+
+def test_tuner_stores_what_it_timed(tmp_path):
+    """Where the operator takes four lanes per site its block size and link loads are given, so a table entry keeps those of
+    an untuned lattice (64 threads, cached), whatever the clock said."""
+    import json
+
+    wanted = []
+    for dims, recon, prec in (((8, 8, 8, 8), 12, "f32"), ((8, 8, 8, 8), 18, "f64"), ((6, 6, 6, 10), 8, "f32"),
+                              ((10, 6, 8, 12), 18, "f32"), ((12, 14, 16, 18), 12, "f32"), ((4, 4, 4, 4), 12, "f32"),
+                              ((6, 8, 10, 12), 18, "f64")):
+        announce(f"tune {dims} {prec} r{recon}")
+        G = gauge(dims, li.near_identity_links(dims, 0.3, 118), prec, recon)
+        assert sp.tune_dslash(G, prec) > 0
+        wanted.append("x".join(map(str, dims)) + ("/l0/r18/v0" if prec == "f64" else f"/l1/r{recon}/v1"))
+    sp.tune_save(str(tmp_path / "t.json"))
+    with open(tmp_path / "t.json") as f:
+        table = json.load(f)
+    for key in wanted:
+        assert (table[key]["nt"], table[key]["stream"]) == (64, 0) and key + "/n4" in table, key
+    sp.release_cache()
