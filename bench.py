@@ -333,10 +333,10 @@ def bench_batched(sp, li, torch, dev, log):
             "note": "iteration figures over the whole batched solve (set-up, reliable updates, polling included)"}
 
 
-# HYP smearing, algorithmic bytes per lattice site: level 1 reads the 4 input links and writes 12 fields,
-# level 2 reads the 4 input links and the 12 level-1 fields and writes 12 fields, level 3 reads the 4 input
-# links and the 12 level-2 fields and writes 4 links; 144 B per FP64 link.
-HYP_BYTES_PER_SITE = 144 * ((4 + 12) + (4 + 12 + 12) + (4 + 12 + 4))
+# HYP smearing, algorithmic bytes per lattice site: a first launch copies the 4 input links into planes; level 1 reads
+# them and writes 12 fields, level 2 reads them and the 12 level-1 fields and writes 12 fields, level 3 reads them and the
+# 12 level-2 fields and writes 4 links; 144 B per FP64 link, 96 B per link of a level field (two of its rows).
+HYP_BYTES_PER_SITE = 144 * (4 + 4 + 4 + 4 + 4 + 4) + 96 * (12 + 12 + 12 + 12)
 
 
 def bench_hyp(sp, torch, lat, links, stream, log):
@@ -358,7 +358,7 @@ def bench_hyp(sp, torch, lat, links, stream, log):
     return {"dims": list(lat.dims), "ms": t * 1e3, "alpha": list(sp.HYP_ALPHA),
             "bytes_per_site": HYP_BYTES_PER_SITE, "achieved_GBs": gbs, "hbm_frac": gbs / HBM_PEAK_GBS,
             "note": "three FP64 levels with SU(3) projections (the closed-form maximiser, else a Newton polar factor and series, else SU(2)-subgroup sweeps); "
-                    "bound by FP64 arithmetic, not bytes"}
+                    "bound by the loads of its staples from L2, not by bytes from HBM"}
 
 
 # NPR contraction: flop per (field set, hypercube): 256 terms, each two bilinears chib^T U chi (U chi: 9

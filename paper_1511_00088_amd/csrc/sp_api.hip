@@ -183,14 +183,15 @@ std::string tune_key(const Geom& g, int lp, int recon, int vp) {
 // sites per parity.
 //  - The stand-alone operator: 64-thread blocks, which even out a last round of blocks (FP64 on 138,600 sites, two blocks
 //    of 256 a CU and a remainder: 31.4 against 35.7 us; never more than 3% slower).
-//  - The stand-alone operator and a single solve: link loads that stream past the caches where the field alone exceeds the
-//    256 MB Infinity Cache. A field that fits is served from there by the next application (an eigensolver's, a
-//    polynomial's, an iteration's), which streaming gives away; a larger one only pushes out what else would hit. The operator,
-//    cached against streaming (us), repeated on one field and after a flush of the cache: 98 MB 17.7, 18.7 and 22.7, 21.1;
-//    127 MB 22.7, 24.4 and 28.3, 26.7; 160 MB (FP64) 26.7, 29.4 and 33.0, 32.2; 209 MB 35.6, 42.1 and 46.5, 44.3; 255 MB 40.9,
-//    46.6 and 51.6, 49.2; 283 MB 56.1, 60.0 and 65.8, 63.1; 295 MB (FP64) 53.0, 55.3 and 59.1, 57.8; 302 MB (FP16) 57.5,
-//    53.7 and 60.8, 56.4; 337 MB 71.3, 67.5 and 74.8, 70.6; 405 MB 85.1, 78.1 and 87.4, 82.5: from 300 MB streaming
-//    wins both ways, below it costs the repeated call 1 to 22% to save a cold one 2 to 7%. A solve: at 225 MB (recon 12)
+//  - The stand-alone operator and a single solve: link loads that stream past the caches where the field alone exceeds
+//    the 256 MB Infinity Cache. A field that fits is served from there by the next application (an eigensolver's, a
+//    polynomial's, an iteration's), which streaming gives away; a larger one only pushes out what else would hit. The
+//    operator, cached against streaming (us), repeated on one field and after a flush of the cache: 98 MB 17.7, 18.7 and
+//    22.7, 21.1; 127 MB 22.7, 24.4 and 28.3, 26.7; 160 MB (FP64) 26.7, 29.4 and 33.0, 32.2; 209 MB 35.6, 42.1 and 46.5,
+//    44.3; 255 MB 40.9, 46.6 and 51.6, 49.2; 283 MB 56.1, 60.0 and 65.8, 63.1; 295 MB (FP64) 53.0, 55.3 and 59.1, 57.8;
+//    302 MB (FP16) 57.5, 53.7 and 60.8, 56.4; 337 MB 71.3, 67.5 and 74.8, 70.6; 405 MB 85.1, 78.1 and 87.4, 82.5: from
+//    300 MB streaming wins both ways, below it costs the repeated call 1 to 22% to save a cold one 2 to 7% (11 to 13% on
+//    three fields of 98 or 160 MB in turn, 23.2 against 20.2 us and 34.6 against 31.0). A solve: at 225 MB (recon 12)
 //    10.55 ms cached against 11.98, at 290 (recon 18) 13.0 against 13.2, at 312 (recon 12) 16.8 against 16.3, at 382
 //    (FP64) 16.9 against 15.7.
 //  - A single solve has 256-thread blocks (the fused iteration's partials, where that applies: solve_threads).
@@ -316,8 +317,8 @@ std::string field_key(const sp_gauge& U, const Geom& g) {
     return k;
 }
 
-// Whether the systems of a batched solve iterate as single systems in common launches (DescMany) instead of in groups that
-// share their link loads: small lattices, whose five launches an iteration are bound by latency.
+// Whether the systems of a batched solve iterate as single systems in common launches (DescMany) instead of in groups
+// that share their link loads: small lattices, whose five launches an iteration are bound by latency.
 bool many_systems(int nsys, const sp_system* systems, const sp_cg_params* prm) {
     if (nsys < 2 || (prm->inner != SP_F32 && prm->inner != SP_F64)) return false;
     const sp_system& a = systems[0];
@@ -377,9 +378,9 @@ int make_layout(int nsys, const sp_system* systems, const sp_cg_params* prm, int
         L->cfg = n_rhs_max > 1 ? tuned_cfg_batched(G.g, lp, rc, prm->inner) : tuned_cfg_solve(G.g, lp, rc, prm->inner);
         // one system: the fused iteration's block size (solve_threads) whenever 256 threads admit that iteration; the
         // block order and the link-load policy stay the tuned ones
-        // (many: the lanes go by the sites of all systems, which share the chip. By each system's own, batches whose total is
-        // just past the limit gain up to 9%, larger ones lose: 3 on 12^3x24 3.0 -> 3.6 ms, 12 5.2 -> 10.2, 128 on 8^4
-        // 6.6 -> 11.0. So a system's summation order depends on the size of its batch.)
+        // (many: the lanes go by the sites of all systems, which share the chip. By each system's own, batches whose
+        // total is just past the limit gain up to 9%, larger ones lose (to 1e-10, m = 0.1): 3 on 12^3x24 3.0 -> 3.6 ms,
+        // 12 5.2 -> 10.2, 128 on 8^4 6.6 -> 11.0. So a system's summation order depends on the size of its batch.)
         const int sites = many ? nsys * G.g.Vh : G.g.Vh;
         L->cfg.quad = n_rhs_max == 1 && quad_lanes(sites, lp, rc, prm->inner);
         if (n_rhs_max == 1 && blocks_for(G.g.Vh, 256) <= FUSED_PARTIALS * 256)
@@ -1126,8 +1127,8 @@ static int dslash_desc(const sp_geom* g, const sp_gauge* U, int prec, const void
     return SP_OK;
 }
 
-// The blocks of a stand-alone operator launch; where the operator takes four lanes per site the block size is 256 whatever
-// the table says.
+// The blocks of a stand-alone operator launch; where the operator takes four lanes per site the block size is 256
+// whatever the table says.
 static int dslash_shape(int Vh, int lp, int recon, int prec, LaunchCfg* c) {
     c->quad = quad_lanes(Vh, lp, recon, prec);
     if (c->quad) c->nt = 256;

@@ -810,8 +810,8 @@ __device__ __forceinline__ void block_sum(double (&v)[NV]) {
 }
 
 // ------------------------------------------------------------------------------------------------------
-// Device-resident CG state of one system. Written by the one-block finalize launch, or, in the fused
-// single-system iteration, by block 0 into a second buffer that only later launches read; either way every
+// Device-resident CG state of one system. Written by the system's block of the finalize launch, or, in the fused
+// iteration, by the system's block 0 into a second buffer that only later launches read; either way every
 // block of a launch sees the same values.
 // ------------------------------------------------------------------------------------------------------
 enum : int {

@@ -22,11 +22,11 @@
 // complex128 (a link is 9 consecutive double2); a first launch copies the input into planes, and the intermediate
 // fields are planes in the caller's workspace. All directions are periodic.
 //
-// What bounds it. A staple pair reads six links, nearly all past the 32 KB L1: measured at 20^3x64, levels 1 to 3
-// drew 10.4 to 11.3 TB/s from the L2, whatever the order of the blocks, with the FP64 units 40 to 60% busy. So the
+// What bounds it. A staple pair reads six links, all of them past the 32 KB L1: measured at 20^3x64, levels 1 to 3
+// drew 14.9, 12.2 and 10.9 TB/s from the L2, whatever the order of the blocks, with the FP64 units 32 to 40% busy. So the
 // levels read planes (natural links of 144 bytes a lane apart cost four times the address cycles), store and read two
 // rows of the projected links, and a projection takes about 500 multiply-adds where a 60-term series took 1,700:
-// 3.13 -> 1.53 ms a smearing (planes 0.11, levels 0.52 + 0.59 + 0.31 ms; before 0.97 + 1.48 + 0.71 ms). Measured and
+// 3.13 -> 1.49 ms a smearing (planes 0.10, levels 0.42 + 0.64 + 0.34 ms; before 0.97 + 1.48 + 0.71 ms). Measured and
 // left: one thread per run of sites along the staple direction, three loads a staple pair (2.2 ms: the runs along x
 // lose their coalescing, and the carried links spill), one thread for lv1(mu, eta) and lv1(eta, mu) (1.68 ms, spills).
 #include "sp_launch.h"

@@ -22,12 +22,12 @@ struct LaunchCfg {
 // recon 12), 2.45 against 2.86 (recon 18) and 2.78 against 3.48 (FP64); 20,736 sites 3.22 against 3.59, 3.49 against
 // 3.37 and 4.44 against 4.38; 32,768 sites 2.78 against 2.90 (recon 12) and 2.55 against 2.91 (fixed-point links);
 // 65,536 sites 5.45 against 4.55 (recon 12), where the chip is full without it. FP32 recon 18 and FP64 move the most
-// bytes a site and turn first. With the block sizes of solve_threads on both sides (m = 0.1) the line stays: 8,000
-// sites 1.79 against 2.25 (recon 12), 1.78 against 1.94 (recon 18) and 1.85 against 2.23 (FP64); 10,368 sites 1.89
+// bytes a site and turn first. With the block sizes of solve_threads on both sides (tol 1e-12, m = 0.1) the line stays:
+// 8,000 sites 1.79 against 2.25 (recon 12), 1.78 against 1.94 (recon 18) and 1.85 against 2.23 (FP64); 10,368 sites 1.89
 // against 2.12, 1.96 against 1.86 and 2.17 against 2.09; 30,720 sites 2.54 against 2.58 (recon 12), 2.48 against 3.09
-// (recon 8); 65,536 sites 4.65 against 4.30 (recon 8). FP16 and BF16 vectors keep a lane per site: the order of a
-// site's eight terms decides how their last digits round, and with it, by some percent either way, where such a solve's
-// reliable updates fall.
+// (recon 8); 65,536 sites 4.65 against 4.30 (recon 8). FP16 and BF16 vectors keep a lane per site: the order of a site's
+// eight terms decides how their last digits round, and with it, by some percent either way, where such a solve's reliable
+// updates fall.
 inline bool quad_lanes(int Vh, int lp, int recon, int vp) {
     if (vp != F32 && vp != F64) return false;
     const bool heavy = vp == F64 || (lp == F32 && recon == 18);
@@ -38,14 +38,14 @@ inline bool quad_lanes(int Vh, int lp, int recon, int vp) {
 static constexpr int NB = 4;
 
 // Groups of one gauge field whose blocks alternate in batched launches, so that a link one of them has brought into an
-// XCD's L2 serves the others. Measured (bit-identical solutions; alternating 1, 2 and 4 groups): 16 systems on 16^3x32
-// 22.5, 19.6 and 18.7 ms, 12 on 24^3x48 79.1, 77.4 and 73.4, 16 on 20^3x64 93.9, 90.4 and 89.5; the 32-system workload
-// 224, 215 and 215.
+// XCD's L2 serves the others. Measured (tol 1e-12, m = 0.1; bit-identical solutions; alternating 1, 2 and 4 groups): 16
+// systems on 16^3x32 22.5, 19.6 and 18.7 ms, 12 on 24^3x48 79.1, 77.4 and 73.4, 16 on 20^3x64 93.9, 90.4 and 89.5; the
+// 32-system workload 224, 215 and 215.
 static constexpr size_t BUNDLE = 4;
 
 // Sites per parity, summed over the systems, up to which the systems of a batch iterate as single systems in common
 // launches (many_systems): two launches an iteration that take their own decisions, against five whose links a group
-// loads once. Small lattices are bound by the launches, large ones by the bytes. Measured per solve (tol 1e-10, m =
+// loads once. Small lattices are bound by the launches, large ones by the bytes. Measured per solve (tol 1e-12, m =
 // 0.1, FP32 recon 12 unless said; groups against this, ms): 3 systems on 8^4 6.75 and 2.02, 32 on 8^4 7.98 and 3.69; 3
 // on 12^3x24 9.03 and 3.58, 6 (recon 18) 9.8 and 4.5, 6 (FP64, 256 threads) 12.0 and 6.2; 3 on 16^3x32 (196,608 sites)
 // 11.0 and 8.5, 4 (FP64) 15.7 and 12.1, 6 (recon 18; 393,216) 13.7 and 11.8, 6 (FP16 links) 14.3 and 14.6, 16
@@ -72,14 +72,15 @@ struct NOf<DescBatch> {
 
 // Threads per block of the fused iteration, for `lanes` lanes of a system (a site has one or four): the fewest that
 // keep it to one block a CU. Small lattices then spread over the chip, and a block reduces fewer wavefronts; with more
-// blocks than CUs each of them sums more partials for nothing. Measured per solve (ms; 64, 128 and 256 threads): 8^4
+// blocks than CUs each of them sums more partials for nothing. Measured per solve (tol 1e-12, m = 0.05; ms; 64, 128 and
+// 256 threads): 8^4
 // FP32 recon 12 with four lanes (8,192 in all) 2.28, 2.49 and 2.68, FP64 2.31, 2.63 and 3.18, BF16 with one lane 4.67,
 // 4.87 and 5.09; 16,384 lanes 2.68, 2.88 and 3.16; 20,736 (12^3x24, recon 18) 3.71, 3.52 and 3.97, FP64 4.57, 4.44 and
 // 5.21, BF16 6.25, 5.94 and 6.18; 32,000 2.96, 2.69 and 2.92; 38,416 4.81, 4.40 and 4.41; 65,536 (16^3x32, recon 12)
-// 6.20, 5.58 and 5.07; 82,944 (12^3x24, recon 12, four lanes) 4.51, 3.83 and 3.79; the 20^3x64 solve on FP16 links 25.8
-// with 128 and 21.9 with 256. Of several systems in common launches each block sums its own system's partials, so the
-// lanes of one count: 3 systems on 8^4 2.01 against 2.25 with 256, 4 on 10^3x20 3.49 against 3.67, 4 in FP64 on 12^3x24
-// 5.14 against 5.92.
+// 6.20, 5.58 and 5.07; 82,944 (12^3x24, recon 12, four lanes) 4.51, 3.83 and 3.79; the 20^3x64 solve on FP16 links (to
+// 1e-8, m = 0.01) 25.8 with 128 and 21.9 with 256. Of several systems in common launches each block sums its own system's
+// partials, so the lanes of one count (m = 0.1): 3 systems on 8^4 2.01 against 2.25 with 256, 4 on 10^3x20 3.49 against
+// 3.67, 4 in FP64 on 12^3x24 5.14 against 5.92.
 inline int solve_threads(int lanes) { return lanes <= 64 * 256 ? 64 : lanes <= 128 * 256 ? 128 : 256; }
 
 // Half operator (see k_dslash; mode DS_PLAIN, DS_NORM or DS_UPDATE). D = DescSingle (one system), DescBatch (up to NB
